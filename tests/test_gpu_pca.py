@@ -70,6 +70,31 @@ def test_workload_components_and_sizes(ci):
             assert np.abs(V[:, a] - V_o[:, a]).max() <= 2e-5 / gap + 1e-5
 
 
+@pytest.mark.parametrize("n,d", [(40, 1), (40, 7), (33, 8), (64, 9), (31, 65), (97, 1023),
+                                 (129, 1025), (300, 2049)])
+def test_components_at_tile_edges(n, d):
+    # edges of the covariance tiles, of the rows per workgroup and of the
+    # staged columns; the data has rank min(3, d), so most of the iterated
+    # directions vanish
+    rng = np.random.default_rng(n + d)
+    k = min(3, d)
+    A = rng.standard_normal((k, d)) * np.array([4.0, 2.0, 1.0])[:k, None]
+    X = (rng.standard_normal((n, k)) @ A + 1.0).astype(np.float32)
+    lam_o, V_o, mu_o = oracle.pca_top2(X) if d > 1 else (np.array([X.var(), 0.0]), None, X.mean(0))
+    lam, mean, V = _gpu_pca(X)
+    say(f"pca edge n={n} d={d}: gpu {lam} oracle {lam_o}")
+    # fp32 covariance sums and a residual of 2e-5 of the largest eigenvalue
+    assert np.allclose(lam, lam_o, rtol=1e-4, atol=2e-5 * lam_o[0])
+    assert np.allclose(mean, mu_o, atol=1e-5)
+    if d > 1:
+        # angle error <= residual / gap to the next value
+        ev = _spectrum(X)
+        for a in range(2):
+            gap = min(abs(ev[a] - ev[b]) for b in range(min(3, d)) if b != a) / ev[0]
+            if gap > 0.02:
+                assert np.abs(V[:, a] - V_o[:, a]).max() <= 2e-5 / gap + 1e-5
+
+
 def test_linear_init_matches_oracle_grid():
     rng = np.random.default_rng(9)
     d = 40
