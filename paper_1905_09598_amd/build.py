@@ -21,6 +21,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libsom.so")
 SOURCES = ["som_api.cpp", "som_train.hip", "som_train_pipe.hip", "som_train_pipe_stream.hip",
+           "som_train_panel.hip",
            "som_eval.hip", "som_util.hip", "som_pca.hip", "som_sparse.hip", "som_batch.hip",
            "som_stream.hip"]
 ARCH = "gfx950"
@@ -49,7 +50,7 @@ def common_flags() -> list:
 # bookkeeping) keeps the exits as real exits.  The streamed pipelined
 # kernels (som_train_pipe_stream.hip) and the sparse kernel poll one load at
 # a time and are built without it.
-UNIFORM_EXIT_SOURCES = ("som_train.hip", "som_train_pipe.hip")
+UNIFORM_EXIT_SOURCES = ("som_train.hip", "som_train_pipe.hip", "som_train_panel.hip")
 
 
 def unit_flags(src: str) -> list:

@@ -40,6 +40,9 @@ struct som_map {
     // per-block sample products of the pipelined training kernel
     float *block_dots = nullptr;
     int64_t block_dots_cap = 0;
+    // panel training: every buffer of a panel, one after the other
+    float *panel = nullptr;
+    int64_t panel_cap = 0;
     // training copy of X with rows padded to a multiple of 4 floats (used
     // when d % 4 != 0 or X is not 16-byte aligned)
     float *xpad = nullptr;
@@ -334,6 +337,7 @@ som_status som_destroy(som_map *m) {
     if (m->order_done) (void)hipEventDestroy(m->order_done);
     (void)hipFree(m->sched);
     (void)hipFree(m->block_dots);
+    (void)hipFree(m->panel);
     (void)hipFree(m->xpad);
     (void)hipFree(m->bwork);
     (void)hipFree(m->sv);
@@ -613,6 +617,45 @@ static bool train_call_ok(const som_schedule *s, int64_t n, int32_t epochs, int6
     return true;
 }
 
+// SOM_DEBUG_ABSENT_WORKGROUP=1 (failure-path tests): one workgroup fewer than
+// the exchanges wait for takes part, so that every exchange wait of the call
+// runs into its time bound and the training ends with SOM_E_TIMEOUT.
+static bool absent_requested() {
+    const char *ab = getenv("SOM_DEBUG_ABSENT_WORKGROUP");
+    return ab && ab[0] == '1' && ab[1] == '\0';
+}
+
+// Training in panels (som_train_panel.hip) when no launch shape was asked for
+// and the build has a panel shape whose buffers fit the cap; *done tells.
+static som_status train_panels(som_map *m, const som_schedule *s, som::TrainArgs &a,
+                               int64_t nsteps, int64_t total, bool *done) {
+    *done = false;
+    if (a.grid || a.variant || a.block_m || a.sweepers || a.lds_rows >= 0) return SOM_OK;
+    int max_lds = 0;
+    hipError_t e = hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock,
+                                         m->device);
+    if (e != hipSuccess) return from_hip(e);
+    som::PanelPlan plan;
+    if (!som::plan_train_panel(m->N, m->d, m->num_cus, max_lds, &plan)) return SOM_OK;
+    const int64_t floats = som::panel_floats(plan, nullptr, nullptr);
+    if ((uint64_t)floats * sizeof(float) > max_bytes()) return SOM_OK;
+    e = stage_steps(m, s, a.n, nsteps, total, a);
+    if (e == hipSuccess) e = ensure(m, &m->panel, &m->panel_cap, floats);
+    if (e != hipSuccess) return from_hip(e);
+    a.grid = plan.controllers;
+    a.slot_spread = 1;  // polls four deep: packed slots
+    e = som::launch_prepare_train(a, m->sched, m->stream);
+    if (e == hipSuccess) e = som::launch_scan_finite(a.X, a.n * m->d, m->state, m->stream);
+    if (e != hipSuccess) return from_hip(e);
+    som::PanelArgs p{};
+    p.t = a;
+    (void)som::panel_floats(plan, &p, m->panel);
+    p.x_vec4 = (m->d % 4 == 0) && (reinterpret_cast<uintptr_t>(a.X) % 16 == 0);
+    p.absent = plan.controllers > 1 && absent_requested() ? 1 : 0;
+    *done = true;
+    return from_hip(som::launch_train_panel(p, plan, m->stream));
+}
+
 som_status som_train(som_map *m, const float *X, int64_t n, int32_t epochs,
                      const som_schedule *s) {
     int64_t nsteps = 0, total = 0;
@@ -624,6 +667,9 @@ som_status som_train(som_map *m, const float *X, int64_t n, int32_t epochs,
     hipError_t e = som::plan_train(a, m->num_cus, &plan);
     if (e == hipErrorInvalidValue) return SOM_E_UNSUPPORTED;
     if (e != hipSuccess) return from_hip(e);
+    bool done = false;
+    const som_status st = train_panels(m, s, a, nsteps, total, &done);
+    if (st != SOM_OK || done) return st;
 
     e = stage_steps(m, s, n, nsteps, total, a);
     if (e != hipSuccess) return from_hip(e);
@@ -663,11 +709,7 @@ som_status som_train(som_map *m, const float *X, int64_t n, int32_t epochs,
     }
     a.grid = plan.grid;
     a.slot_spread = plan.slot_spread;
-    // SOM_DEBUG_ABSENT_WORKGROUP=1 (failure-path tests): launch one workgroup
-    // fewer than the exchanges wait for, so that every exchange wait of the
-    // call runs into its time bound and the kernel ends with SOM_E_TIMEOUT.
-    const char *ab = getenv("SOM_DEBUG_ABSENT_WORKGROUP");
-    if (ab && ab[0] == '1' && ab[1] == '\0' && plan.grid > 1) plan.absent = 1;
+    if (plan.grid > 1 && absent_requested()) plan.absent = 1;
     e = som::launch_prepare_train(a, m->sched, m->stream);
     if (e == hipSuccess) e = som::launch_scan_finite(X, n * m->d, m->state, m->stream);
     if (e == hipSuccess) e = som::launch_train(a, plan, m->stream);

@@ -99,6 +99,46 @@ double plan_train_pipe(const TrainArgs &a, int num_cus, int max_lds, TrainPlan *
 int64_t pipe_block_dots_floats(int m, int64_t nsteps);
 hipError_t launch_train_pipe(const TrainArgs &a, const TrainPlan &plan, hipStream_t s);
 
+// Panel training (som_train_panel.hip): the same steps with the pass over the
+// prototypes as two matrix products per panel of m steps.
+struct PanelPlan {
+    int32_t instance = -1;    // kernel instance
+    int32_t m = 0;            // steps per panel
+    int32_t controllers = 0;  // workgroups that run a panel's steps
+    int32_t ctl_rows = 0;     // units of a controller whose coefficients LDS holds
+    int32_t lds = 0;          // bytes of LDS of the control launch
+    int32_t dpad = 0;         // d rounded up to whole gather tasks
+    int32_t npad = 0;         // rows of the per-unit arrays
+    int32_t ksplit = 1;       // column ranges of the pass over the prototypes
+    int32_t gsplit = 1;       // column ranges of the Gram matrices
+    int32_t prep = 0;         // tasks that prepare a panel
+    int32_t grid = 0;         // workgroups of the exchanging kernel
+};
+// Buffers are indexed by panel modulo their number.
+struct PanelArgs {
+    TrainArgs t;
+    float *ec[2];     // (m + 1) x dpad: column set less the centre, and the centre
+    float *xt[4];     // dpad x m: the steps' samples, transposed
+    float *gm[3];     // gsplit x (m x m + 16): column set by own steps
+    float *gx[3];     // the same by the panel before's steps
+    float *prod[2];   // ksplit x npad x m: the sweep's products
+    double *qf[2];    // ksplit x npad: its squared norms
+    float *gam[2];    // (m / 16) x npad x 16: coefficients of the panel's steps
+    float *beta[2];   // (m / 16) x npad
+    double *pc, *qc;  // npad x m, npad: products and Q at the panel's start
+    double *qn, *qe;   // npad: Q carried to the next panel; its estimate at the start
+    unsigned *arrived;  // grid barrier of the exchanging kernel
+    int32_t dpad, npad, ksplit, gsplit, prep, controllers, ctl_rows;
+    int32_t correct;  // products are corrected by a launch of their own
+    int32_t x_vec4;   // sample rows are whole aligned float4s
+    int32_t absent;   // controllers that leave at once (failure-path tests)
+};
+// The panel shape for N units of d floats; false when the build has none.
+bool plan_train_panel(int32_t N, int32_t d, int num_cus, int max_lds, PanelPlan *plan);
+// Floats of a plan's buffers; with p, also sets its pointers from base.
+int64_t panel_floats(const PanelPlan &plan, PanelArgs *p, float *base);
+hipError_t launch_train_panel(const PanelArgs &a, const PanelPlan &plan, hipStream_t s);
+
 // Host-side launchers (each translation unit owns its kernels).
 hipError_t plan_train(const TrainArgs &a, int num_cus, TrainPlan *plan);
 hipError_t launch_train(const TrainArgs &a, const TrainPlan &plan, hipStream_t s);

@@ -1,0 +1,200 @@
+"""Panel training (the default path of som_train) against the fp64 oracle at
+the edges of its shapes: units per lane and per workgroup, steps per 16 and per
+panel, columns per tile and per gather, one and several control workgroups;
+and its error paths."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1905_09598_amd as som
+import workloads
+from gpu_util import dev, rel_gap, say
+
+pytestmark = pytest.mark.gpu
+
+GAP = 1e-4
+ENV = ("SOM_TRAIN_VARIANT", "SOM_TRAIN_GRID", "SOM_TRAIN_BLOCK_M", "SOM_TRAIN_LDS_ROWS",
+       "SOM_TRAIN_SWEEPERS")
+
+
+@pytest.fixture(autouse=True)
+def _default_path(monkeypatch):
+    for k in ENV:
+        monkeypatch.delenv(k, raising=False)
+
+
+def _train(rows, cols, d, n, topology=som.RECT, sched=(0.4, 0.02, None, 0.5), offset=0, seed=5,
+           step0=0, total=0):
+    X = workloads.gaussian_mixture(n, d, 3, 0.2, seed=seed + d)
+    W0 = workloads.random_weights(rows * cols, d, seed + 1, -1.0, 1.0)
+    order = workloads.epoch_orders(n, 1, seed)
+    lr0, lr1, s0, s1 = sched
+    s0 = max(rows, cols) / 2.0 if s0 is None else s0
+    m = som.Map(rows, cols, d, seed=0, topology=topology)
+    m.weights = dev(W0)
+    flat = dev(np.concatenate([np.zeros(offset, np.float32), X.reshape(-1)]))
+    Xd = flat[offset:].view(n, d)
+    trace = dev(np.full(n, -1, np.int32))
+    m.train(Xd, 1, lr0, lr1, s0, s1, order=dev(order), bmu_trace=trace, step0=step0,
+            total_steps=total)
+    W = m.weights.cpu().numpy().astype(np.float64)
+    got = trace.cpu().numpy()
+    m.close()
+    s = oracle.schedule(lr0, lr1, s0, s1)
+    Wo, tr = oracle.train(W0, rows, cols, X, order, s, topology=topology, trace=True, step0=step0,
+                          total_steps=total or step0 + n)
+    if np.array_equal(got, tr):
+        # 1e-7 relative rounding per panel of values up to a few units
+        assert np.abs(W - Wo).max() <= 2e-5
+        return
+    k = int(np.argmax(got != tr))
+    Wk, _ = oracle.train(W0, rows, cols, X, order[:k], s, topology=topology, step0=step0,
+                         total_steps=total or step0 + n)
+    Ds = np.sort(oracle.distances(Wk, X[order[k]]))
+    say(f"  identical BMUs for {k}/{n} steps")
+    # A distance is the difference of fp32 sums at the scale S of squared
+    # sample-to-sample distances, each within about 8 roundings of 2^-24 S: two
+    # distances closer than 1e-6 S are not told apart (short rows and many
+    # units put many prototypes that close to a sample).
+    S = np.square(X.astype(np.float64) - X[order[0]]).sum(1).max()
+    assert len(Ds) > 1 and (Ds[1] - Ds[0] <= GAP * Ds[0] or Ds[1] - Ds[0] <= 1e-6 * S), \
+        "divergence without a near tie"
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 1), (1, 15), (4, 4), (1, 17), (8, 8), (5, 13),
+                                       (15, 17), (16, 16), (1, 257), (16, 32), (27, 19),
+                                       (32, 32), (5, 205), (41, 43), (50, 50), (128, 129)])
+@pytest.mark.parametrize("topology", [som.RECT, som.HEX])
+def test_unit_counts_follow_the_oracle(rows, cols, topology):
+    say("panel units", rows, cols, topology)
+    _train(rows, cols, 40, 175, topology)
+
+
+@pytest.mark.parametrize("rows,cols", [(9, 11), (20, 21), (31, 30), (60, 50)])
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 31, 47, 48, 49, 63, 64, 65, 79, 80, 81, 97, 160,
+                               161, 241])
+def test_step_counts_follow_the_oracle(rows, cols, n):
+    say("panel steps", rows, cols, n)
+    _train(rows, cols, 24, n, seed=n)
+
+
+@pytest.mark.parametrize("rows,cols", [(9, 11), (60, 50)])
+@pytest.mark.parametrize("d,offset", [(1, 0), (3, 0), (4, 0), (5, 1), (16, 0), (31, 0), (32, 3),
+                                      (63, 0), (64, 0), (65, 0), (129, 0), (1023, 0), (1024, 1),
+                                      (1025, 0), (2049, 0), (4545, 0)])
+def test_row_lengths_and_alignments_follow_the_oracle(rows, cols, d, offset):
+    say("panel columns", rows, cols, d, offset)
+    _train(rows, cols, d, 90 if d < 2000 else 50, offset=offset)
+
+
+@pytest.mark.parametrize("rows,cols", [(9, 11), (60, 50)])
+def test_resumed_steps_follow_the_oracle(rows, cols):
+    _train(rows, cols, 32, 100, step0=37, total=500)
+
+
+@pytest.mark.parametrize("rows,cols", [(7, 9), (25, 30), (60, 50)])
+def test_exact_copies_and_untouched_units(rows, cols):
+    # lr = 1 and sigma = 0: the BMU becomes the sample and nothing else moves
+    n, d = 170, 20
+    X = workloads.gaussian_mixture(n, d, 4, 0.3, seed=8)
+    W0 = workloads.random_weights(rows * cols, d, 9, -1.0, 1.0)
+    order = np.arange(n, dtype=np.int32)
+    m = som.Map(rows, cols, d, seed=0)
+    m.weights = dev(W0)
+    trace = dev(np.full(n, -1, np.int32))
+    m.train(dev(X), 1, 1.0, 1.0, 0.0, 0.0, order=dev(order), bmu_trace=trace)
+    got, W = trace.cpu().numpy(), m.weights.cpu().numpy()
+    m.close()
+    want = W0.copy()
+    for k, c in enumerate(got):
+        want[c] = X[k]
+    assert np.array_equal(W, want)
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 300), (33, 32), (60, 50)])
+def test_equal_units_take_the_lowest_index(rows, cols):
+    # every prototype equal: each step's BMU is unit 0 while sigma is infinite
+    X = workloads.gaussian_mixture(40, 12, 2, 0.3, seed=3)
+    m = som.Map(rows, cols, 12, seed=0)
+    m.weights = dev(np.zeros((rows * cols, 12), np.float32))
+    trace = dev(np.full(40, -1, np.int32))
+    m.train(dev(X), 1, 0.3, 0.3, np.inf, np.inf, order=dev(np.arange(40, dtype=np.int32)),
+            bmu_trace=trace)
+    assert np.array_equal(trace.cpu().numpy(), np.zeros(40, np.int32))
+    m.close()
+
+
+@pytest.mark.parametrize("rows,cols", [(9, 11), (25, 30), (60, 50)])
+def test_unusable_input_leaves_the_prototypes(rows, cols):
+    n, d = 200, 37
+    X = workloads.gaussian_mixture(n, d, 3, 0.2, seed=d)
+    W = workloads.random_weights(rows * cols, d, 4)
+    bad = X.copy()
+    bad[150, 36] = np.inf
+    wrong = np.arange(n, dtype=np.int32)
+    wrong[120] = n
+    for data, order, name in ((bad, np.arange(n, dtype=np.int32), "SOM_E_NONFINITE"),
+                              (X, wrong, "SOM_E_BAD_ORDER")):
+        m = som.Map(rows, cols, d, seed=0)
+        m.weights = dev(W)
+        m.train(dev(data), 1, 0.5, 0.05, 3.0, 0.5, order=dev(order))
+        with pytest.raises(som.SomError) as e:
+            m.synchronize()
+        assert e.value.name == name
+        assert np.array_equal(m.weights.cpu().numpy(), W)
+        m.close()
+
+
+def test_exchange_timeout_ends_the_grid_and_is_reported(monkeypatch):
+    rows, cols, d, n = 60, 50, 64, 200
+    X = workloads.gaussian_mixture(n, d, 3, 0.2, seed=7)
+    W = workloads.random_weights(rows * cols, d, 8)
+    order = dev(workloads.epoch_orders(n, 1, 9))
+    m = som.Map(rows, cols, d, seed=0)
+    m.weights = dev(W)
+    monkeypatch.setenv("SOM_DEBUG_EXCHANGE_TIMEOUT_US", "5000")
+    monkeypatch.setenv("SOM_DEBUG_ABSENT_WORKGROUP", "1")
+    m.train(dev(X), 1, 0.5, 0.05, 3.0, 0.5, order=order)
+    with pytest.raises(som.SomError) as e:
+        m.synchronize()
+    assert e.value.name == "SOM_E_TIMEOUT"
+    m.synchronize()
+    monkeypatch.delenv("SOM_DEBUG_ABSENT_WORKGROUP")
+    monkeypatch.delenv("SOM_DEBUG_EXCHANGE_TIMEOUT_US")
+    out = []
+    for _ in range(2):
+        m.weights = dev(W)
+        m.train(dev(X), 1, 0.5, 0.05, 3.0, 0.5, order=order)
+        m.synchronize()
+        out.append(m.weights.cpu().numpy())
+    assert np.array_equal(out[0], out[1])
+    m.close()
+
+
+@pytest.mark.parametrize("rows,cols,d,n", [(10, 10, 500, 400), (30, 30, 300, 300),
+                                           (60, 50, 300, 300)])
+def test_memory_cap_takes_the_grid_kernels(rows, cols, d, n, monkeypatch):
+    # below the panels' buffers the call still trains, on the kernels that
+    # need none
+    X = workloads.gaussian_mixture(n, d, 3, 0.2, seed=2)
+    W = workloads.random_weights(rows * cols, d, 3)
+    order = dev(workloads.epoch_orders(n, 1, 1))
+    traces = []
+    for cap in (None, "100000"):
+        m = som.Map(rows, cols, d, seed=0)
+        m.weights = dev(W)
+        if cap:
+            monkeypatch.setenv("SOM_MAX_BYTES", cap)
+        t = dev(np.full(n, -1, np.int32))
+        m.train(dev(X), 1, 0.4, 0.05, 4.0, 0.7, order=order, bmu_trace=t)
+        traces.append(t.cpu().numpy())
+        monkeypatch.delenv("SOM_MAX_BYTES", raising=False)
+        m.close()
+    o = oracle.train(W, rows, cols, X, workloads.epoch_orders(n, 1, 1),
+                     oracle.schedule(0.4, 0.05, 4.0, 0.7), trace=True)[1]
+    k = min(int(np.argmax(t != o)) if np.any(t != o) else n for t in traces)
+    if k < n:
+        Wk, _ = oracle.train(W, rows, cols, X, workloads.epoch_orders(n, 1, 1)[:k],
+                             oracle.schedule(0.4, 0.05, 4.0, 0.7), total_steps=n)
+        D = np.sort(oracle.distances(Wk, X[workloads.epoch_orders(n, 1, 1)[k]]))
+        assert rel_gap(D[:1], D[1:2])[0] <= GAP
