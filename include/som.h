@@ -224,13 +224,17 @@ som_status som_train_batch(som_map *map, const float *X, int64_t n, int32_t epoc
 
 /* Batched BMU assignment (Sec. 8A): for each of the n rows of the device
  * matrix X, out_idx[i] = BMU index (lowest index among equal minima).
- * Candidates are ranked with fp32 matrix-core products
- * ||w||^2 - 2 x.w (the product split over ranges of d, and the ranges
- * summed in order, when there are too few samples to fill the chip
- * otherwise); the four best by that score are re-ranked by direct fp32
- * distances.  Scratch (candidate lists of 32 bytes per sample and unit
- * group, or 512 bytes per sample, range and 128 units of partial products
- * when d is split) is kept by the map.
+ * Candidates are ranked with matrix-core products ||w||^2 - 2 x.w (split
+ * over ranges of d, and the ranges summed in order, when there are too few
+ * samples to fill the chip otherwise); the four best by that score are
+ * re-ranked by direct fp32 distances.  The products are fp32, or for large
+ * calls fp16 instructions on operands held in two fp16 halves, whose error
+ * against fp64 is no larger; rows that halves cannot hold (a NaN, an
+ * infinity, magnitudes above 2^40, samples below 2^-40) are ranked in fp32.
+ * Scratch (candidate lists of 32 bytes per sample and unit group, or 512
+ * bytes per sample, range and 128 units of partial products when d is split;
+ * for the halves 4 bytes per prototype element and per element of up to
+ * 256 MiB of samples at a time) is kept by the map.
  * out_idx is a device int32 array of n entries.  Stream-ordered. */
 som_status som_bmu(som_map *map, const float *X, int64_t n, int32_t *out_idx);
 
@@ -242,7 +246,7 @@ som_status som_bmu2(som_map *map, const float *X, int64_t n, int32_t *out_idx,
 
 /* As som_bmu2, for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the same kernels and the same outputs, but no hipMalloc, hipFree or
+ * the same search with its products in fp32 and the same outputs, but no hipMalloc, hipFree or
  * allocating library routine is called.  The call's scratch (the
  * prototypes' squared norms, the BMUs when out_idx is NULL, the candidate
  * lists, and the partial products when the search splits d) lives in one

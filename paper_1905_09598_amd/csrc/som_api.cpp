@@ -64,6 +64,11 @@ struct som_map {
     int64_t cand_cap = 0;
     float *part = nullptr;
     int64_t part_cap = 0;
+    // the search's rows in halves: samples (one chunk) and prototypes, with
+    // their scales; w_bad follows the prototypes' scales
+    void *xhalf = nullptr, *whalf = nullptr;
+    float *xscale = nullptr, *wscale = nullptr;
+    int64_t xhalf_cap = 0, whalf_cap = 0, xscale_cap = 0, wscale_cap = 0;
     float *d1 = nullptr;
     double *sums = nullptr;
     int64_t eval_cap = 0;
@@ -221,6 +226,61 @@ som_status check_deferred(som_map *m) {
     return SOM_OK;
 }
 
+// The search with its products on the fp16 matrix instructions, one chunk of
+// samples after the other (the halves of a chunk stay in the Infinity Cache
+// between being written and read).
+som_status run_eval_half(som_map *m, som::EvalArgs a, const som::HalfPlan &h, int32_t *idx1,
+                         int32_t *idx2, float *d1) {
+    const float *X = a.X;
+    const int64_t n = a.n;
+    const int64_t rows = n < h.chunk ? n : h.chunk;
+    a.splits = h.splits;
+    a.split_len = h.split_len;
+    a.ugroups = h.ugroups;
+    a.group_units = h.group_units;
+    a.slabs = h.slabs;
+    a.tiles_u = (a.N + som::kHalfUnits - 1) / som::kHalfUnits;
+    const int64_t ncand = h.splits > 1 ? 0 : rows * (int64_t)h.ugroups * som::kCand * 2;
+    const int64_t npart =
+        h.splits > 1 ? (int64_t)h.splits * rows * a.tiles_u * som::kHalfUnits : 0;
+    som_status st = ensure_eval_scratch(m, rows, ncand, npart);
+    if (st != SOM_OK) return st;
+    const int64_t xh = som::half_rows_halves(rows, a.d, som::kHalfSamples);
+    const int64_t wh = som::half_rows_halves(a.N, a.d, som::kHalfUnits);
+    hipError_t e = ensure(m, reinterpret_cast<_Float16 **>(&m->xhalf), &m->xhalf_cap, xh);
+    if (e == hipSuccess) e = ensure(m, reinterpret_cast<_Float16 **>(&m->whalf), &m->whalf_cap, wh);
+    if (e == hipSuccess) e = ensure(m, &m->xscale, &m->xscale_cap, rows);
+    if (e == hipSuccess) e = ensure(m, &m->wscale, &m->wscale_cap, (int64_t)a.N + 1);
+    if (e != hipSuccess) return from_hip(e);
+    a.wnorm = m->wnorm;
+    a.cand = m->cand;
+    a.part = m->part;
+    a.xhalf = static_cast<const _Float16 *>(m->xhalf);
+    a.whalf = static_cast<const _Float16 *>(m->whalf);
+    a.xscale = m->xscale;
+    a.wscale = m->wscale;
+    int32_t *bad = reinterpret_cast<int32_t *>(m->wscale + a.N);
+    a.w_bad = bad;
+    a.x_vec4 = (m->d % 4 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0);
+    e = som::launch_row_sqnorm(m->W, m->ld, m->N, m->wnorm, bad, m->stream);
+    if (e == hipSuccess)
+        e = som::launch_split_rows(m->W, a.N, m->ld, a.d, som::kHalfUnits, m->whalf, m->wscale, bad,
+                                   m->stream);
+    for (int64_t at = 0; at < n && e == hipSuccess; at += h.chunk) {
+        a.n = n - at < h.chunk ? n - at : h.chunk;
+        a.X = X + at * a.d;
+        a.tiles_s = (int32_t)((a.n + som::kHalfSamples - 1) / som::kHalfSamples);
+        a.idx1 = idx1 + at;
+        a.idx2 = idx2 ? idx2 + at : nullptr;
+        a.d1 = d1 ? d1 + at : nullptr;
+        e = som::launch_split_rows(a.X, a.n, a.d, a.d, som::kHalfSamples, m->xhalf, m->xscale,
+                                   nullptr, m->stream);
+        if (e == hipSuccess) e = som::launch_bmu_half(a, m->stream);
+        if (e == hipSuccess) e = som::launch_bmu_rerank(a, m->stream);
+    }
+    return from_hip(e);
+}
+
 som_status run_eval(som_map *m, const float *X, int64_t n, int32_t *idx1,
                     int32_t *idx2, float *d1) {
     som::EvalArgs a{};
@@ -233,7 +293,11 @@ som_status run_eval(som_map *m, const float *X, int64_t n, int32_t *idx1,
     a.topology = m->topology;
     a.X = X;
     a.n = n;
-    if (!som::plan_bmu_candidates(&a, m->num_cus, max_bytes())) return SOM_E_OOM;
+    double fp32_us = 0.0;
+    if (!som::plan_bmu_candidates(&a, m->num_cus, max_bytes(), &fp32_us)) return SOM_E_OOM;
+    som::HalfPlan half;
+    if (som::plan_bmu_half(&a, m->num_cus, max_bytes(), fp32_us, &half))
+        return run_eval_half(m, a, half, idx1, idx2, d1);
     som_status st = ensure_eval_scratch(m, n, som::bmu_cand_ints(a), som::bmu_part_floats(a));
     if (st != SOM_OK) return st;
     a.wnorm = m->wnorm;
@@ -243,7 +307,7 @@ som_status run_eval(som_map *m, const float *X, int64_t n, int32_t *idx1,
     a.idx2 = idx2;
     a.d1 = d1;
     a.x_vec4 = (m->d % 4 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0);
-    hipError_t e = som::launch_row_sqnorm(m->W, m->ld, m->N, m->wnorm, m->stream);
+    hipError_t e = som::launch_row_sqnorm(m->W, m->ld, m->N, m->wnorm, nullptr, m->stream);
     if (e == hipSuccess) e = som::launch_bmu_candidates(a, m->stream);
     if (e == hipSuccess) e = som::launch_bmu_rerank(a, m->stream);
     return from_hip(e);
@@ -349,6 +413,10 @@ som_status som_destroy(som_map *m) {
     (void)hipFree(m->wnorm);
     (void)hipFree(m->cand);
     (void)hipFree(m->part);
+    (void)hipFree(m->xhalf);
+    (void)hipFree(m->whalf);
+    (void)hipFree(m->xscale);
+    (void)hipFree(m->wscale);
     (void)hipFree(m->idx1);
     (void)hipFree(m->idx2);
     (void)hipFree(m->d1);
@@ -896,7 +964,7 @@ som_status som_bmu2_noalloc(som_map *m, const float *X, int64_t n, int32_t *out_
     a.idx2 = out_idx2;
     a.d1 = out_d1;
     a.x_vec4 = (m->d % 4 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0);
-    e = som::launch_row_sqnorm(m->W, m->ld, m->N, wnorm, m->stream);
+    e = som::launch_row_sqnorm(m->W, m->ld, m->N, wnorm, nullptr, m->stream);
     if (e == hipSuccess) e = som::launch_bmu_candidates(a, m->stream);
     if (e == hipSuccess) e = som::launch_bmu_rerank(a, m->stream);
     return from_hip(e);

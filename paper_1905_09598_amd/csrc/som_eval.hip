@@ -330,7 +330,19 @@ __global__ __launch_bounds__(64 * kRerankWaves) void bmu_rerank_kernel(EvalArgs 
     int lu[kCand];
 #pragma unroll
     for (int c = 0; c < kCand; ++c) { ls[c] = INFINITY; lu[c] = -1; }
-    if (a.splits > 1) {
+    if (a.xhalf && (a.xscale[i] < 0.f || *a.w_bad != 0)) {
+        // the sample, or a prototype, could not be split into halves: every
+        // score in fp32 (such rows hold infinities, NaN or extreme values)
+        const float *x = a.X + i * a.d;
+        for (int u = 0; u < a.N; ++u) {
+            const float *w = a.W + (int64_t)u * a.ld;
+            float s = 0.f;
+            for (int64_t j = lane; j < a.d; j += 64) s = fmaf(x[j], w[j], s);
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
+            if (lane == 0) insert_top(ls, lu, a.wnorm[u] - 2.f * s, u);
+        }
+    } else if (a.splits > 1) {
         // each lane's best units among 4 q .. 4 q + 3, q = lane, lane + 64, ...
         const int64_t np = (int64_t)a.tiles_u * kBN;
         const int nq = (a.N + 3) / 4;
@@ -508,13 +520,14 @@ hipError_t noalloc_scratch(void **ptr) {
 // MI355X), for `slots` co-resident workgroups.  Workgroups run in rounds;
 // each costs its slices plus a fixed start and finish.
 namespace {
+constexpr double kSliceUs = 4.3;      // the unit
 constexpr double kWgFixed = 0.6;      // first loads, candidate merge, stores
 constexpr double kPairCost = 2e-6;    // per (score, unit) pair the re-rank merges
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 }  // namespace
 
-bool plan_bmu_candidates(EvalArgs *a, int num_cus, uint64_t max_scratch_bytes) {
+bool plan_bmu_candidates(EvalArgs *a, int num_cus, uint64_t max_scratch_bytes, double *us) {
     const int64_t slots = 2 * (int64_t)(num_cus > 0 ? num_cus : 1);
     const int64_t tiles_s = ceil_div(a->n, kBM);
     const int64_t tiles_u = ceil_div(a->N, kBN);
@@ -556,6 +569,7 @@ bool plan_bmu_candidates(EvalArgs *a, int num_cus, uint64_t max_scratch_bytes) {
             a->group_units = 0;
         }
     }
+    if (us) *us = best * kSliceUs;
     return best < 1e300;
 }
 

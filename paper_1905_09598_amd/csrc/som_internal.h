@@ -154,8 +154,8 @@ hipError_t launch_prepare_train(const TrainArgs &a, float2 *sched, hipStream_t s
 // or infinity among the `count` floats at x.
 hipError_t launch_scan_finite(const float *x, int64_t count, DevState *state,
                               hipStream_t s);
-// out[u] = |W[u]|^2 for the N rows of W.
-hipError_t launch_row_sqnorm(const float *W, int64_t ld, int32_t N, float *out,
+// out[u] = |W[u]|^2 for the N rows of W; *clear (nullable) = 0.
+hipError_t launch_row_sqnorm(const float *W, int64_t ld, int32_t N, float *out, int32_t *clear,
                              hipStream_t s);
 // Copy the n x d rows of X into out, rows of xld floats (xld >= d, a
 // multiple of 4), zero past d.
@@ -180,15 +180,39 @@ struct EvalArgs {
     int32_t *idx2;          // n (nullable)
     float *d1;              // n (nullable)
     int32_t x_vec4;
+    // products on the fp16 matrix instructions (som_eval_half.hip); null
+    // otherwise
+    const _Float16 *xhalf, *whalf;  // the rows' halves
+    const float *xscale, *wscale;   // their scales (a sample's is -1 where it has none)
+    const int32_t *w_bad;           // nonzero: some prototype has none
+    int32_t slabs;                  // slabs of 32 columns
 };
 constexpr int kCand = 4;
+constexpr int kHalfSamples = 256, kHalfUnits = 128;  // the fp16 kernels' tile
+
+// Shape of a search on the fp16 matrix instructions, for chunks of samples.
+struct HalfPlan {
+    int64_t chunk = 0;
+    int32_t splits = 1, split_len = 0, ugroups = 0, group_units = 0, slabs = 0;
+};
+// True (and *plan set) when that is expected to take less than fp32_us.
+bool plan_bmu_half(EvalArgs *a, int num_cus, uint64_t max_bytes, double fp32_us, HalfPlan *plan);
+// Halves that `rows` rows take, stored in whole tiles of `tile` rows.
+int64_t half_rows_halves(int64_t rows, int32_t d, int tile);
+// Split the rows of X (row pitch ld) into out, their scales into scale;
+// any_bad (nullable) is raised by a row that cannot be split.
+hipError_t launch_split_rows(const float *X, int64_t rows, int64_t ld, int32_t d, int tile,
+                             void *out, float *scale, int32_t *any_bad, hipStream_t s);
+hipError_t launch_bmu_half(const EvalArgs &a, hipStream_t s);
 
 // The candidate search's shape for n samples over N units on `num_cus`
 // compute units (sets ugroups, group_units, splits, split_len, tiles_s,
 // tiles_u): the fewest rounds of workgroups, among the shapes whose
 // candidate lists and partial products fit in max_scratch_bytes.  False
 // when none does.
-bool plan_bmu_candidates(EvalArgs *a, int num_cus, uint64_t max_scratch_bytes);
+// *us (nullable): the expected microseconds.
+bool plan_bmu_candidates(EvalArgs *a, int num_cus, uint64_t max_scratch_bytes,
+                         double *us = nullptr);
 // Scratch of a planned search: int32 entries of the candidate lists and
 // floats of the partial products (0 for the fused form).
 int64_t bmu_cand_ints(const EvalArgs &a);

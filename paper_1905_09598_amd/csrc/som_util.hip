@@ -116,24 +116,26 @@ __global__ void scan_finite_kernel(const float *x, int64_t count, DevState *stat
     }
 }
 
-// out[u] = sum_j W[u][j]^2 (fp32, fixed order): `tpr` threads per row (64,
-// 128 or 256; 256 / tpr rows per workgroup), 16-byte loads, four in flight.
+// out[u] = sum_j W[u][j]^2 (fp64 sums in a fixed order, rounded once): `tpr`
+// threads per row (64, 128 or 256; 256 / tpr rows per workgroup), 16-byte
+// loads, four in flight.
 __global__ __launch_bounds__(256) void row_sqnorm_kernel(const float *W, int64_t ld, int32_t N,
-                                                         float *out, int tpr) {
-    __shared__ float part[4];
+                                                         float *out, int tpr, int32_t *clear) {
+    __shared__ double part[4];
+    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
     const int rsub = threadIdx.x / tpr, t = threadIdx.x - rsub * tpr;
     const int64_t row = (int64_t)blockIdx.x * (256 / tpr) + rsub;
-    float acc = 0.f;
+    double acc = 0.0;
     if (row < N) {
         const float4 *w = reinterpret_cast<const float4 *>(W + row * ld);
         const int64_t n4 = ld / 4;
 #pragma unroll 4
         for (int64_t j = t; j < n4; j += tpr) {
             const float4 v = w[j];
-            acc = fmaf(v.x, v.x, acc);
-            acc = fmaf(v.y, v.y, acc);
-            acc = fmaf(v.z, v.z, acc);
-            acc = fmaf(v.w, v.w, acc);
+            acc = fma((double)v.x, (double)v.x, acc);
+            acc = fma((double)v.y, (double)v.y, acc);
+            acc = fma((double)v.z, (double)v.z, acc);
+            acc = fma((double)v.w, (double)v.w, acc);
         }
     }
 #pragma unroll
@@ -142,9 +144,9 @@ __global__ __launch_bounds__(256) void row_sqnorm_kernel(const float *W, int64_t
     __syncthreads();
     if (t == 0 && row < N) {
         const int w0 = threadIdx.x >> 6, nw = tpr / 64;
-        float s = part[w0];
+        double s = part[w0];
         for (int k = 1; k < nw; ++k) s += part[w0 + k];
-        out[row] = s;
+        out[row] = (float)s;
     }
 }
 
@@ -194,12 +196,12 @@ hipError_t launch_scan_finite(const float *x, int64_t count, DevState *state,
     return hipGetLastError();
 }
 
-hipError_t launch_row_sqnorm(const float *W, int64_t ld, int32_t N, float *out,
+hipError_t launch_row_sqnorm(const float *W, int64_t ld, int32_t N, float *out, int32_t *clear,
                              hipStream_t s) {
     const int64_t n4 = ld / 4;
     const int tpr = n4 > 512 ? 256 : n4 > 128 ? 128 : 64;
     const int64_t blocks = ((int64_t)N + 256 / tpr - 1) / (256 / tpr);
-    row_sqnorm_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(W, ld, N, out, tpr);
+    row_sqnorm_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(W, ld, N, out, tpr, clear);
     return hipGetLastError();
 }
 

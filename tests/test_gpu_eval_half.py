@@ -1,0 +1,96 @@
+"""The batched BMU of large calls (products on the fp16 matrix instructions, every
+operand in two halves) against the oracle at the edges of its tiles, and
+against the fp32 products (som_bmu2_noalloc) for rows that cannot be split."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1905_09598_amd as som
+import workloads
+from gpu_util import dev, rel_gap, say, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+GAP = 1e-4
+
+
+def _case(rows, cols, d, n, seed):
+    X = workloads.gaussian_mixture(n, d, 8, 0.2, seed)
+    W = workloads.random_weights(rows * cols, d, seed + 1, -1.0, 1.0)
+    k = rows * cols // 2
+    W[:k] = 0.6 * X[:k] + 0.4 * W[:k]
+    return X, W
+
+
+# sample tiles of 256, unit tiles of 128, slabs of 32 columns; the larger
+# shapes take several chunks or unit groups, the longer rows split columns
+@pytest.mark.parametrize("rows,cols,d,n,offset", [
+    (32, 40, 700, 12032, 0),      # whole tiles
+    (31, 41, 701, 12033, 0),      # remainders everywhere, rows not whole float4s
+    (32, 40, 703, 12031, 1),      # misaligned samples
+    (50, 50, 96, 33000, 0),
+    (1, 1281, 640, 9000, 3),
+    (70, 72, 1025, 4200, 0),
+    (25, 41, 4000, 2600, 0),
+])
+def test_large_calls_match_oracle(rows, cols, d, n, offset):
+    say("half products", rows, cols, d, n, offset)
+    torch = torch_cuda()
+    X, W = _case(rows, cols, d, n, d)
+    m = som.Map(rows, cols, d, seed=0)
+    m.weights = dev(W)
+    flat = dev(np.concatenate([np.zeros(offset, np.float32), X.reshape(-1)]))
+    Xd = flat[offset:].view(n, d)
+    idx, idx2, d1 = m.bmu(Xd, second=True)
+    again, qe, te = m.evaluate(Xd)
+    assert torch.equal(idx, again)
+    o = oracle.evaluate(W, rows, cols, X)
+    gap = rel_gap(o["d1"], o["d2"])
+    clear = gap > GAP
+    assert clear.mean() > 0.9
+    idx = idx.cpu().numpy()
+    assert np.array_equal(idx[clear], o["c1"][clear])
+    # the distances are direct fp32 sums
+    same = idx == o["c1"]
+    got = d1.cpu().numpy()
+    assert np.abs(got[same] - o["d1"][same]).max() <= 1e-5 * o["d1"].max()
+    assert abs(qe - o["qe"]) <= 1e-5 * o["qe"]
+    m.close()
+
+
+@pytest.mark.parametrize("where", ["samples", "prototypes", "both"])
+def test_rows_that_cannot_be_split_match_the_fp32_products(where):
+    rows, cols, d, n = 32, 40, 700, 12000
+    X, W = _case(rows, cols, d, n, 11)
+    special = [np.inf, -np.inf, np.nan, 3e38, -1e30, 1e-30, 1e-42, 2.0 ** 41, 2.0 ** -45]
+    if where in ("samples", "both"):
+        for k, v in enumerate(special):
+            X[100 * k + 7, 3 * k] = v
+            X[100 * k + 8] = 0.0
+            X[100 * k + 8, 5 * k + 1] = v        # the row's only entry
+            X[100 * k + 9] *= np.float32(v if np.isfinite(v) and abs(v) < 1e20 else 1e-20)
+    if where in ("prototypes", "both"):
+        few = special if where == "both" else special[5:7] + special[8:]
+        for k, v in enumerate(few):
+            W[50 * k + 3] *= np.float32(1e-20)
+            W[50 * k + 4, 2 * k] = v
+            W[50 * k + 5] = 0.0
+    n_small = 1500 if where != "samples" else n   # (a bad prototype is searched slowly)
+    m = som.Map(rows, cols, d, seed=0)
+    m.weights = dev(W)
+    Xd = dev(X)
+    a = [t.cpu().numpy() for t in m.bmu(Xd, second=True)]
+    torch = torch_cuda()
+    b = [torch.empty(n, dtype=t, device="cuda") for t in (torch.int32, torch.int32, torch.float32)]
+    som.som_bmu2_noalloc(m.handle, Xd, n, *b)
+    m.synchronize()
+    b = [t.cpu().numpy() for t in b]
+    differ = np.nonzero(a[0] != b[0])[0]
+    say("unsplittable", where, "differing BMUs", differ.size, "of", n, n_small)
+    # equal units, or distances equal within fp32 rounding of a direct sum
+    for i in differ:
+        assert np.isfinite(a[2][i]) and abs(a[2][i] - b[2][i]) <= 1e-5 * abs(b[2][i]), i
+    both = np.isfinite(a[2]) & np.isfinite(b[2])
+    assert np.array_equal(np.isfinite(a[2]), np.isfinite(b[2]))
+    assert np.allclose(a[2][both], b[2][both], rtol=1e-5)
+    m.close()
