@@ -293,6 +293,15 @@ som_status run_eval(som_map *m, const float *X, int64_t n, int32_t *idx1,
     a.topology = m->topology;
     a.X = X;
     a.n = n;
+    if (som::bmu_few(a) && (uint64_t)n * m->N * sizeof(float) <= max_bytes()) {
+        const som_status st = ensure_eval_scratch(m, n, 0, n * m->N);
+        if (st != SOM_OK) return st;
+        a.idx1 = idx1;
+        a.idx2 = idx2;
+        a.d1 = d1;
+        a.x_vec4 = (m->d % 4 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0);
+        return from_hip(som::launch_bmu_few(a, m->part, m->stream));
+    }
     double fp32_us = 0.0;
     if (!som::plan_bmu_candidates(&a, m->num_cus, max_bytes(), &fp32_us)) return SOM_E_OOM;
     som::HalfPlan half;

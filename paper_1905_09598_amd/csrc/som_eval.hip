@@ -457,6 +457,101 @@ __global__ __launch_bounds__(64 * kRerankWaves) void bmu_rerank_kernel(EvalArgs 
     }
 }
 
+// A call of a few samples: the direct distances of every unit, one wave per
+// unit and up to NS samples, in the order the re-rank sums them, into
+// dist[sample][N].  One read of the prototypes is all that such a call needs
+// (100 MB, about 20 us, for one sample on 50 x 50 units of 10000 floats); the
+// norms, a product on tiles of 64 samples and the re-rank of its partial sums
+// took 17 + 54 + 62 us there.
+template <int NS>
+__global__ __launch_bounds__(256) void few_distances_kernel(EvalArgs a, float *dist) {
+    const int lane = threadIdx.x & 63;
+    const int64_t u = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t s0 = (int64_t)blockIdx.y * NS;
+    if (u >= a.N) return;
+    const float *w = a.W + u * a.ld;
+    const float *x[NS];
+    float acc[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        x[k] = a.X + (s0 + k < a.n ? s0 + k : a.n - 1) * a.d;
+        acc[k] = 0.f;
+    }
+    int64_t j0 = 0;
+    if (a.x_vec4) {
+        const int64_t d4 = a.d / 4;
+#pragma unroll 4
+        for (int64_t j = lane; j < d4; j += 64) {
+            const f4 wv = reinterpret_cast<const f4 *>(w)[j];
+#pragma unroll
+            for (int k = 0; k < NS; ++k) {
+                const f4 df = reinterpret_cast<const f4 *>(x[k])[j] - wv;
+                acc[k] = fmaf(df[0], df[0], acc[k]);
+                acc[k] = fmaf(df[1], df[1], acc[k]);
+                acc[k] = fmaf(df[2], df[2], acc[k]);
+                acc[k] = fmaf(df[3], df[3], acc[k]);
+            }
+        }
+        j0 = d4 * 4;
+    }
+#pragma unroll 4
+    for (int64_t j = j0 + lane; j < a.d; j += 64) {
+        const float wv = w[j];
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            const float df = x[k][j] - wv;
+            acc[k] = fmaf(df, df, acc[k]);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) acc[k] += __shfl_xor(acc[k], o, 64);
+        if (lane == 0 && s0 + k < a.n) dist[(s0 + k) * a.N + u] = acc[k];
+    }
+}
+
+// The best and second best unit by (distance, unit) of sample blockIdx.x (a NaN
+// is no distance).
+constexpr int kFewBlock = 1024;
+__global__ __launch_bounds__(kFewBlock) void few_best_kernel(EvalArgs a, const float *dist) {
+    __shared__ unsigned long long best[2][kFewBlock / 64];
+    const int64_t i = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const float *row = dist + i * a.N;
+    unsigned long long k1 = ~0ull, k2 = ~0ull;  // (distance bits, unit), ascending
+    for (int u = threadIdx.x; u < a.N; u += kFewBlock) {
+        const float v = row[u];
+        if (v != v) continue;
+        const unsigned long long k =
+            ((unsigned long long)__float_as_uint(v) << 32) | (unsigned)u;  // v >= +0
+        if (k < k1) {
+            k2 = k1;
+            k1 = k;
+        } else if (k < k2) {
+            k2 = k;
+        }
+    }
+    const auto merge = [&](unsigned long long o1, unsigned long long o2) {
+        const unsigned long long hi = k1 > o1 ? k1 : o1;
+        k1 = k1 < o1 ? k1 : o1;
+        k2 = k2 < o2 ? k2 : o2;
+        k2 = k2 < hi ? k2 : hi;
+    };
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) merge(__shfl_xor(k1, o, 64), __shfl_xor(k2, o, 64));
+    if (lane == 0) {
+        best[0][wave] = k1;
+        best[1][wave] = k2;
+    }
+    __syncthreads();
+    if (threadIdx.x > 0) return;
+    for (int w = 1; w < kFewBlock / 64; ++w) merge(best[0][w], best[1][w]);
+    a.idx1[i] = k1 == ~0ull ? -1 : (int)(unsigned)k1;
+    if (a.idx2) a.idx2[i] = k2 == ~0ull ? -1 : (int)(unsigned)k2;
+    if (a.d1) a.d1[i] = k1 == ~0ull ? INFINITY : __uint_as_float((unsigned)(k1 >> 32));
+}
+
 // One workgroup sums sqrt(d1) and the count of non-adjacent (idx1, idx2)
 // pairs in fp64, with a fixed thread-to-sample map and reduction tree.
 constexpr int kReduceBlock = 1024;
@@ -603,6 +698,26 @@ hipError_t launch_bmu_candidates(const EvalArgs &a, hipStream_t s) {
 hipError_t launch_bmu_rerank(const EvalArgs &a, hipStream_t s) {
     const int64_t blocks = (a.n + kRerankWaves - 1) / kRerankWaves;
     bmu_rerank_kernel<<<dim3((unsigned)blocks), dim3(64 * kRerankWaves), 0, s>>>(a);
+    return hipGetLastError();
+}
+
+// Up to 8 samples (two reads of the prototypes, the second from the Infinity
+// Cache): the direct search's 20-40 us lie below the tiled search's 130 at 100 MB
+// of prototypes, and its two launches below the tiled search's three always.
+bool bmu_few(const EvalArgs &a) { return a.n <= 8; }
+
+hipError_t launch_bmu_few(const EvalArgs &a, float *dist, hipStream_t s) {
+    const unsigned units = (unsigned)((a.N + 3) / 4);
+    if (a.n == 1)
+        few_distances_kernel<1><<<dim3(units), dim3(256), 0, s>>>(a, dist);
+    else if (a.n == 2)
+        few_distances_kernel<2><<<dim3(units), dim3(256), 0, s>>>(a, dist);
+    else
+        few_distances_kernel<4>
+            <<<dim3(units, (unsigned)((a.n + 3) / 4)), dim3(256), 0, s>>>(a, dist);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    few_best_kernel<<<dim3((unsigned)a.n), dim3(kFewBlock), 0, s>>>(a, dist);
     return hipGetLastError();
 }
 

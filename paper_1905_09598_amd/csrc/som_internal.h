@@ -223,6 +223,10 @@ hipError_t launch_bmu_candidates(const EvalArgs &a, hipStream_t s);
 constexpr size_t kNoAllocScratchBytes = 8u << 20;
 hipError_t noalloc_scratch(void **ptr);
 hipError_t launch_bmu_rerank(const EvalArgs &a, hipStream_t s);
+// Calls of a few samples: the direct distances of all units (dist: n x N
+// floats of scratch), then the best two.
+bool bmu_few(const EvalArgs &a);
+hipError_t launch_bmu_few(const EvalArgs &a, float *dist, hipStream_t s);
 // QE and TE sums over n samples from (idx1, idx2, d1); writes 2 doubles.
 hipError_t launch_qe_te_reduce(const int32_t *idx1, const int32_t *idx2,
                                const float *d1, int64_t n, int32_t cols,

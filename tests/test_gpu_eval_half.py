@@ -1,4 +1,5 @@
-"""The batched BMU of large calls (products on the fp16 matrix instructions, every
+"""The batched BMU of the smallest calls (direct distances of every unit) and of
+large ones (products on the fp16 matrix instructions, every
 operand in two halves) against the oracle at the edges of its tiles, and
 against the fp32 products (som_bmu2_noalloc) for rows that cannot be split."""
 import numpy as np
@@ -94,3 +95,29 @@ def test_rows_that_cannot_be_split_match_the_fp32_products(where):
     assert np.array_equal(np.isfinite(a[2]), np.isfinite(b[2]))
     assert np.allclose(a[2][both], b[2][both], rtol=1e-5)
     m.close()
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 1), (1, 2), (5, 1), (9, 7), (33, 31), (70, 70)])
+@pytest.mark.parametrize("d,offset", [(1, 0), (3, 1), (4, 0), (255, 0), (256, 0), (1030, 3)])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 8, 9])
+def test_few_samples_match_oracle(rows, cols, d, offset, n):
+    rng = np.random.default_rng(rows + d + n)
+    X = rng.standard_normal((n, d)).astype(np.float32)
+    W = rng.standard_normal((rows * cols, d)).astype(np.float32)
+    if rows * cols > 4:
+        W[4] = W[2]                    # an exact tie goes to the lower unit
+        X[0] = W[2]
+    m = som.Map(rows, cols, d, seed=0)
+    m.weights = dev(W)
+    flat = dev(np.concatenate([np.zeros(offset, np.float32), X.reshape(-1)]))
+    idx, idx2, d1 = [t.cpu().numpy() for t in m.bmu(flat[offset:].view(n, d), second=True)]
+    m.close()
+    o = oracle.evaluate(W, rows, cols, X)
+    clear = rel_gap(o["d1"], o["d2"]) > GAP
+    assert np.array_equal(idx[clear], o["c1"][clear])
+    # a direct fp32 sum of d terms in 64 lanes and a tree
+    assert np.abs(d1 - o["d1"]).max() <= 1e-5 * max(o["d1"].max(), 1e-30)
+    if rows * cols == 1:
+        assert (idx2 == -1).all()
+    if rows * cols > 4:
+        assert (idx[0], idx2[0]) == (2, 4) and d1[0] == 0.0
