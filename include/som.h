@@ -214,7 +214,8 @@ som_status som_train_csr(som_map *map, const int64_t *indptr, const int32_t *ind
  * after the BMU is fp64: per-unit sample sums, then the lattice Gaussian as
  * a blur along the lattice columns and then along the rows (it factors over
  * the two axes).  Work memory of (2 + P) N (d + 1) + rows^2 + P cols^2
- * doubles (P = 1 for RECT, 3 for HEX) is kept by the map.  Stream-ordered.
+ * doubles (P = 1 for RECT, 3 for HEX), and n + N / 64 more when P N (d + 1) is
+ * less than that, is kept by the map.  Stream-ordered.
  * Errors: SOM_E_ARG (map or X NULL, n <= 0 or above 2^31 - 1, epochs <= 0,
  * sigma < 0 or NaN, a bad decay kind, an exponential decay with a zero or
  * infinite endpoint, X not covering n * d floats), SOM_E_UNSUPPORTED (d

@@ -876,7 +876,7 @@ som_status som_train_batch(som_map *m, const float *X, int64_t n, int32_t epochs
     s.sigma_decay = sigma_decay;
     if (!schedule_ok(&s)) return SOM_E_ARG;
     if (!device_range_ok(X, (uint64_t)n * (uint64_t)m->d * sizeof(float))) return SOM_E_ARG;
-    const size_t work = som::batch_work_doubles(m->rows, m->cols, m->d, m->topology);
+    const size_t work = som::batch_work_doubles(m->rows, m->cols, m->d, m->topology, n);
     if (((uint64_t)m->d + 1 + 63) / 64 > 65535) return SOM_E_UNSUPPORTED;
     if ((uint64_t)work * sizeof(double) > max_bytes()) return SOM_E_OOM;
     hipError_t e = ensure(m, &m->bwork, &m->bwork_cap, (int64_t)work);

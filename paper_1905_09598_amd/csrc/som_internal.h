@@ -277,11 +277,11 @@ struct BatchArgs {
     int64_t n;
     int32_t d, rows, cols, topology;
     double sigma;           // the epoch's radius
-    double *work;           // batch_work_doubles(rows, cols, d, topology)
+    double *work;           // batch_work_doubles(rows, cols, d, topology, n)
     float *W;               // N x ld prototypes, updated in place
     int64_t ld;
 };
-size_t batch_work_doubles(int32_t rows, int32_t cols, int32_t d, int32_t topology);
+size_t batch_work_doubles(int32_t rows, int32_t cols, int32_t d, int32_t topology, int64_t n);
 hipError_t launch_batch_epoch(const BatchArgs &b, hipStream_t s);
 
 // In-place stream over `bytes` (a multiple of 16) of buf on `grid`

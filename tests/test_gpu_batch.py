@@ -75,6 +75,26 @@ def test_batch_epochs_match_oracle(rows, cols, d, n, topology):
     _check_epochs(rows, cols, d, n, 3, max(rows, cols) / 2.0, 0.7, topology)
 
 
+@pytest.mark.parametrize("topology", [som.RECT, som.HEX])
+@pytest.mark.parametrize("rows,cols,d,n", [
+    (1, 1, 1, 3000),       # the sample lists do not fit in the blurs' arrays
+    (2, 3, 3, 2049),
+    (8, 8, 126, 1023),     # one group of units; edges of the sums' columns
+    (13, 5, 127, 1024),
+    (5, 26, 128, 1025),
+    (16, 17, 254, 40),     # edges of the blurs' columns and stages
+    (17, 16, 255, 9),
+    (15, 33, 256, 8),
+    (65, 64, 7, 7),
+])
+def test_batch_epochs_at_tile_edges(rows, cols, d, n, topology):
+    say("batch edges", rows, cols, d, n, topology)
+    # the last radius keeps every weight above exp(-(65^2 + 64^2) / 18) = 1e-201:
+    # at 0.7 a few samples leave far units weights below 1e-308, which the
+    # factored Gaussian and the oracle's underflow at different places
+    _check_epochs(rows, cols, d, n, 2, max(rows, cols) / 2.0, 3.0, topology, seed=n)
+
+
 def _random_batch_cases(seed, count):
     """Random (rows, cols, d, n, topology): lattices up to 48 x 48 and rows
     of up to 1500 floats, with N^2 d bounded for the oracle's explicit
