@@ -213,17 +213,18 @@ som_status ensure_eval_scratch(som_map *m, int64_t n, int64_t ncand, int64_t npa
     return SOM_OK;
 }
 
+// Report (and clear) the status a copy of the map's status words holds.
+som_status take_status(som_map *m, const som::DevState &st) {
+    if (st.status == 0) return SOM_OK;
+    const int32_t zero = 0;
+    const hipError_t e = hipMemcpy(&m->state->status, &zero, sizeof(zero), hipMemcpyHostToDevice);
+    return e != hipSuccess ? from_hip(e) : (som_status)st.status;
+}
+
 som_status check_deferred(som_map *m) {
     som::DevState st;
-    hipError_t e = hipMemcpy(&st, m->state, sizeof(st), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return from_hip(e);
-    if (st.status != 0) {
-        const int32_t zero = 0;
-        e = hipMemcpy(&m->state->status, &zero, sizeof(zero), hipMemcpyHostToDevice);
-        if (e != hipSuccess) return from_hip(e);
-        return (som_status)st.status;
-    }
-    return SOM_OK;
+    const hipError_t e = hipMemcpy(&st, m->state, sizeof(st), hipMemcpyDeviceToHost);
+    return e != hipSuccess ? from_hip(e) : take_status(m, st);
 }
 
 // The search with its products on the fp16 matrix instructions, one chunk of
@@ -378,15 +379,19 @@ som_status som_create(int32_t rows, int32_t cols, int32_t d, uint64_t seed,
         e = hipDeviceGetAttribute(&m->num_cus, hipDeviceAttributeMultiprocessorCount,
                                   m->device);
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&m->W), bytes);
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&m->state), sizeof(som::DevState));
+    // the status words, and behind them the evaluation's two sums: an
+    // evaluation reads both in one copy
+    if (e == hipSuccess)
+        e = hipMalloc(reinterpret_cast<void **>(&m->state),
+                      sizeof(som::DevState) + 2 * sizeof(double));
     if (e == hipSuccess) e = hipMemset(m->state, 0, sizeof(som::DevState));
+    m->sums = reinterpret_cast<double *>(m->state + 1);
     if (e == hipSuccess)
         e = hipMalloc(reinterpret_cast<void **>(&m->slots),
                       (size_t)som::kSlotWords * sizeof(unsigned long long));
     // prototype norms, roundup(N, 4) floats: the re-rank reads them as float4
     if (e == hipSuccess)
         e = hipMalloc(reinterpret_cast<void **>(&m->wnorm), (size_t)((N + 3) & ~3) * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&m->sums), 2 * sizeof(double));
     if (e == hipSuccess) e = hipEventCreateWithFlags(&m->order_done, hipEventDisableTiming);
     if (e == hipSuccess) e = som::launch_init_uniform(m->W, ld, m->N, d, seed, nullptr);
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -429,7 +434,6 @@ som_status som_destroy(som_map *m) {
     (void)hipFree(m->idx1);
     (void)hipFree(m->idx2);
     (void)hipFree(m->d1);
-    (void)hipFree(m->sums);
     delete m;
     return SOM_OK;
 }
@@ -994,15 +998,19 @@ static som_status qe_te(som_map *m, const float *X, int64_t n, int32_t *out_idx,
     if (st != SOM_OK) return st;
     hipError_t e = som::launch_qe_te_reduce(out_idx ? out_idx : m->idx1, m->idx2, m->d1, n,
                                             m->cols, m->topology, m->sums, m->stream);
-    double h[2] = {0.0, 0.0};
+    struct {
+        som::DevState state;
+        double sums[2];
+    } h{};
+    static_assert(sizeof(h) == sizeof(som::DevState) + 2 * sizeof(double), "as allocated");
     if (e == hipSuccess)
-        e = hipMemcpyAsync(h, m->sums, sizeof(h), hipMemcpyDeviceToHost, m->stream);
+        e = hipMemcpyAsync(&h, m->state, sizeof(h), hipMemcpyDeviceToHost, m->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
     if (e != hipSuccess) return from_hip(e);
-    st = check_deferred(m);
+    st = take_status(m, h.state);
     if (st != SOM_OK) return st;
-    if (qe) *qe = h[0] / (double)n;
-    if (te) *te = h[1] / (double)n;
+    if (qe) *qe = h.sums[0] / (double)n;
+    if (te) *te = h.sums[1] / (double)n;
     return SOM_OK;
 }
 
