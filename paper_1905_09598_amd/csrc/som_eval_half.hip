@@ -286,13 +286,15 @@ __global__ __launch_bounds__(kHThreads, 2) void half_partial_kernel(EvalArgs a) 
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 constexpr size_t kHalfLds = 2 * (size_t)kSlabHalves * sizeof(_Float16);
-// Microseconds of one slab of a tile on a workgroup (measured 1.7 with a
-// workgroup on every compute unit), of one workgroup's start and finish, and of
-// the two extra launches; the rows are split at about 3 TB/s.  The line against
-// the fp32 kernels lies where these add up to less than their measured 4.3 us
-// per slice of half the samples and twice the columns: at 20 x 20 units, 2000
-// samples of 2000 floats the fp32 kernel (46 us) stays ahead.
-constexpr double kSlabUs = 1.7, kTileUs = 6.0, kLaunchUs = 8.0;
+// Microseconds of one slab of a tile on a workgroup (1.2 on few tiles, up to 1.7
+// with every compute unit busy), of one workgroup's start and finish, and of the
+// two extra launches; the rows are split at about 3 TB/s.  The line against the
+// fp32 kernels lies where these add up to less than those kernels' measured
+// 4.3 us per slice.  Evaluations on either side, fp32 and halves in
+// microseconds: 23,395 samples of 303 on 12 x 32 units 219 and 164, 17,406 of 71
+// on 15 x 34 172 and 125, 1,307 of 186 on 52 x 100 120 and 90; at 2,000 of 2,000
+// on 20 x 20 units the fp32 kernel (46 us) stays.
+constexpr double kSlabUs = 1.2, kTileUs = 3.0, kLaunchUs = 3.0;
 constexpr int64_t kChunkBytes = 256 << 20;  // samples split at a time
 
 }  // namespace
