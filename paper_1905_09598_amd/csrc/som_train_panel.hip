@@ -692,6 +692,11 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
     // rows of 16 lanes that hold units, of the 4 NW of the workgroup
     const int lanes = (min(a.N - base, Lds::kUnits) + U - 1) / U;
     const bool waits = (lane & (4 * NW - 1)) * 16 < lanes;
+    // A wave without units leaves here: it would publish no keys, so nothing
+    // would keep the other waves from overwriting, two steps on, those it
+    // still waits for.
+    if (!GRID && wave * 64 >= lanes) return true;
+    const int wave_rows = min((lanes - wave * 64 + 15) / 16, 4);  // rows with units
 
     for (int sub = 0; sub * kSub < nst; ++sub) {
         // ---- L columns of the 16 steps
@@ -845,7 +850,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
                 const int rm = row_min_i32(m);
                 bool win = m == rm && base + mine < a.N;
                 const unsigned long long wins = __ballot(win);
-                if (__builtin_popcountll(wins) > 4)  // equal distances in a row
+                if (__builtin_popcountll(wins) > wave_rows)  // equal distances in a row
                     win = win && (((wins >> (lane & 48)) & ((1ull << i) - 1)) == 0);
                 const unsigned tag = 0x80u | (unsigned)(k >> 1) | ((unsigned)sub << 3);
                 unsigned long long *slots = keys + (k & 1) * 4 * NW,

@@ -124,6 +124,46 @@ def test_equal_units_take_the_lowest_index(rows, cols):
     m.close()
 
 
+# The nearest prototypes are copies in the last units, in a row of 16 lanes of a
+# wave that has fewer than four such rows with units.
+@pytest.mark.parametrize("rows,cols,copies", [(3, 6, 2), (5, 5, 4), (16, 17, 16), (20, 20, 3),
+                                              (21, 32, 8)])
+def test_equal_units_of_a_partly_filled_wave(rows, cols, copies):
+    N, d, n = rows * cols, 24, 70
+    W0 = workloads.random_weights(N, d, 3, 4.0, 5.0)
+    W0[-copies:] = W0[-1] - 4.0
+    m = som.Map(rows, cols, d, seed=0)
+    m.weights = dev(W0)
+    trace = dev(np.full(n, -1, np.int32))
+    X = workloads.random_weights(n, d, 4, 0.0, 1.0)
+    inf = float("inf")  # every unit moves alike, so the copies stay equal
+    m.train(dev(X), 1, 0.01, 0.01, inf, inf, order=dev(np.arange(n, dtype=np.int32)),
+            bmu_trace=trace)
+    assert np.array_equal(trace.cpu().numpy(), np.full(n, N - copies, np.int32))
+    m.close()
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 1), (4, 4), (8, 8), (10, 10), (16, 17), (23, 23)])
+def test_long_runs_with_waves_without_units(rows, cols):
+    # sigma = inf: each prototype is the moving average of the samples, whatever
+    # the BMUs.  2e-5: rounding of 1e-7 per panel at values of a few units,
+    # shrunk by (1 - lr) a step.
+    d, n, epochs, lr = 128, 640, 10, 0.05
+    X = workloads.gaussian_mixture(n, d, 3, 0.2, seed=9)
+    W0 = workloads.random_weights(rows * cols, d, 2, -1.0, 1.0)
+    order = np.concatenate([np.arange(n, dtype=np.int32)] * epochs)
+    m = som.Map(rows, cols, d, seed=0)
+    m.weights = dev(W0)
+    inf = float("inf")
+    m.train(dev(X), epochs, lr, lr, inf, inf, order=dev(order))
+    W = m.weights.cpu().numpy().astype(np.float64)
+    m.close()
+    want = W0.astype(np.float64)
+    for k in order:
+        want += lr * (X[k].astype(np.float64) - want)
+    assert np.abs(W - want).max() <= 2e-5
+
+
 @pytest.mark.parametrize("rows,cols", [(9, 11), (25, 30), (60, 50)])
 def test_unusable_input_leaves_the_prototypes(rows, cols):
     n, d = 200, 37
