@@ -481,7 +481,7 @@ static som::TrainArgs train_args(som_map *m, const float *X, int64_t n) {
     if (a.grid < 0) a.grid = 0;
     if (a.grid > som::kMaxTrainGrid) a.grid = som::kMaxTrainGrid;
     // SOM_TRAIN_VARIANT: 1 LDS-resident, 2 streamed, 3 / 4 pipelined LDS /
-    // streamed, 5 never pipelined.
+    // streamed, 5 never pipelined; 6 asks for panels (panels_requested).
     const char *v = getenv("SOM_TRAIN_VARIANT");
     a.variant = (v && *v) ? atoi(v) : 0;
     if (a.variant < 0 || a.variant > 5) a.variant = 0;
@@ -706,12 +706,22 @@ static bool absent_requested() {
     return ab && ab[0] == '1' && ab[1] == '\0';
 }
 
-// Training in panels (som_train_panel.hip) when no launch shape was asked for
-// and the build has a panel shape whose buffers fit the cap; *done tells.
+// SOM_TRAIN_VARIANT=6: panels wherever the build has a shape for them.
+static bool panels_requested() {
+    const char *v = getenv("SOM_TRAIN_VARIANT");
+    return v && v[0] == '6' && v[1] == '\0';
+}
+
+// Training in panels (som_train_panel.hip) when no launch shape was asked for,
+// the persistent kernel would take longer and the build has a panel
+// shape whose buffers fit the cap; *done tells.
 static som_status train_panels(som_map *m, const som_schedule *s, som::TrainArgs &a,
-                               int64_t nsteps, int64_t total, bool *done) {
+                               const som::TrainPlan &persistent, int64_t nsteps, int64_t total,
+                               bool *done) {
     *done = false;
     if (a.grid || a.variant || a.block_m || a.sweepers || a.lds_rows >= 0) return SOM_OK;
+    if (!panels_requested() && som::persistent_train_faster(m->N, m->d, nsteps, persistent))
+        return SOM_OK;
     int max_lds = 0;
     hipError_t e = hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock,
                                          m->device);
@@ -749,7 +759,7 @@ som_status som_train(som_map *m, const float *X, int64_t n, int32_t epochs,
     if (e == hipErrorInvalidValue) return SOM_E_UNSUPPORTED;
     if (e != hipSuccess) return from_hip(e);
     bool done = false;
-    const som_status st = train_panels(m, s, a, nsteps, total, &done);
+    const som_status st = train_panels(m, s, a, plan, nsteps, total, &done);
     if (st != SOM_OK || done) return st;
 
     e = stage_steps(m, s, n, nsteps, total, a);

@@ -1209,6 +1209,30 @@ bool plan_train_panel(int32_t N, int32_t d, int num_cus, int max_lds, PanelPlan 
     return false;
 }
 
+// The pipelined kernel with its rows in LDS pays the grid exchange a step and
+// little else while a workgroup has few rows; one workgroup's panels cost more
+// a step with every 256 units, and the panels of larger maps pay an exchange too.
+// Measured, microseconds per step of that kernel and of panels: 625 units of
+// 1024 floats 1.34 and 1.27, 676 of 64 1.27 and 1.27, 784 of 64 1.27 and 1.33,
+// 1024 of 2048 1.41 and 1.59; 2500 of 1024 1.46 and 2.24; 2500 of 3072 (the
+// longest rows of its instances for short samples) 2.07 and 2.58, 1024 of 4608
+// 2.30 and 1.64; up to 512 floats 40 rows a workgroup (10000 of 512) 2.33 and
+// 2.46, 46 rows (11664 of 512) 2.66 and 2.48; longer rows 25 a workgroup (6400
+// of 1024) 2.29 and 2.55, 32 rows (8100 of 1024) 2.85 and 2.57.  The other
+// kernels lose at every size measured: 4900 of 1536, streamed, 3.04 and 2.56.
+// Short calls pay for the panels' preparation, the first pass and the last.
+// Microseconds per call: 10000 units of 2048, 80 steps 422 and 445, 160 steps
+// 761 and 674; 2500 of 5000, 80 steps 383 and 384; 900 of 5000, 20 steps 90 and
+// 97, 40 steps 132 and 119; 400 of 2000, 2 steps 49 and 51, 5 steps 54 and 50;
+// 100 of 500, 1 step 45 and 38.
+bool persistent_train_faster(int32_t N, int32_t d, int64_t nsteps, const TrainPlan &plan) {
+    if (nsteps < (N > 1024 ? 96 : d > 2048 ? 40 : d > 1024 ? 4 : 1)) return true;
+    constexpr int kOneWorkgroup = 700, kRowLength = 3072;
+    const int rows = d <= 512 ? 40 : 28;
+    return plan.variant == 3 && N > kOneWorkgroup && d <= kRowLength &&
+           (N + plan.grid - 1) / plan.grid <= rows;
+}
+
 int64_t panel_floats(const PanelPlan &pl, PanelArgs *p, float *base) {
     PanelArgs none{};
     PanelArgs &a = p ? *p : none;

@@ -1,4 +1,4 @@
-"""Panel training (the default path of som_train) against the fp64 oracle at
+"""Panel training (asked for, and where the default takes it) against the fp64 oracle at
 the edges of its shapes: units per lane and per workgroup, steps per 16 and per
 panel, columns per tile and per gather, one and several control workgroups;
 and its error paths."""
@@ -18,9 +18,10 @@ ENV = ("SOM_TRAIN_VARIANT", "SOM_TRAIN_GRID", "SOM_TRAIN_BLOCK_M", "SOM_TRAIN_LD
 
 
 @pytest.fixture(autouse=True)
-def _default_path(monkeypatch):
+def _panels(monkeypatch):
     for k in ENV:
         monkeypatch.delenv(k, raising=False)
+    monkeypatch.setenv("SOM_TRAIN_VARIANT", "6")
 
 
 def _train(rows, cols, d, n, topology=som.RECT, sched=(0.4, 0.02, None, 0.5), offset=0, seed=5,
@@ -85,6 +86,18 @@ def test_step_counts_follow_the_oracle(rows, cols, n):
 def test_row_lengths_and_alignments_follow_the_oracle(rows, cols, d, offset):
     say("panel columns", rows, cols, d, offset)
     _train(rows, cols, d, 90 if d < 2000 else 50, offset=offset)
+
+
+# Both sides of the lines between panels and the persistent kernel: units of one
+# workgroup, rows per workgroup at two row lengths, the longest row, and steps.
+@pytest.mark.parametrize("rows,cols,d,n", [
+    (20, 35, 60, 100), (1, 701, 60, 100), (80, 128, 8, 100), (19, 539, 8, 100),
+    (67, 107, 516, 100), (1, 7169, 513, 100), (27, 26, 3072, 100), (27, 26, 3073, 100),
+    (128, 129, 8, 95), (128, 129, 8, 96), (5, 6, 2049, 39), (5, 6, 2049, 40), (5, 6, 1025, 3),
+    (5, 6, 1025, 4), (5, 6, 1024, 1)])
+def test_default_path_at_its_lines(rows, cols, d, n, monkeypatch):
+    monkeypatch.delenv("SOM_TRAIN_VARIANT")
+    _train(rows, cols, d, n)
 
 
 @pytest.mark.parametrize("rows,cols", [(9, 11), (60, 50)])
