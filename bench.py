@@ -3,7 +3,7 @@
 
 One bench step is one pass of the whole hot path over the workload:
 reset the map to its seeded initial prototypes, train it for the workload's
-full schedule (epochs * n per-sample steps in one persistent kernel), then
+full schedule (epochs * n per-sample steps, all on the device), then
 assign every sample to its BMU and compute QE and TE (one batched MFMA BMU
 search, som_evaluate).  Data, order and initial prototypes are resident in
 HBM before timing starts.
@@ -28,7 +28,9 @@ traffic's rate against `stream_inplace`, an in-place stream over a buffer
 of W's size on the training grid measured in the same run.  `bound` comes
 from the launch plan: the LDS-resident kernels never stream W and wait on
 the grid exchange ("latency"), the streamed ones stream W once per block
-("hbm").
+("hbm").  Training in panels, the default on every workload, touches W once
+per 48-80 steps and waits on its steps' chain ("latency"); `traffic` is then
+null.
 `cpu_baseline` times the fp64 oracle on the host over a bounded prefix of
 the same training run.
 """
@@ -460,6 +462,13 @@ def measure(cfg, input_kind: str, steps: int, warmup: int):
     # the LDS-resident kernels keep W on chip and wait on the grid exchange;
     # the streamed ones read and write W once per block of steps
     bound = "hbm" if plan["variant"] in (0, 2, 4) else "latency"
+    # every workload of the table trains in panels unless a launch shape is
+    # forced: their steps wait on each other through LDS, or on the exchange
+    # between the control workgroups beyond 1,024 units
+    panels = not sparse and not any(k.startswith("SOM_TRAIN_") for k in os.environ)
+    if panels:
+        kernel_name = "panel_step_kernel" if cfg.units <= 1024 else "panel_grid_kernel"
+        variant, bound, traffic = "panels", "latency", None
     if sparse:
         # the sparse path's own bytes: the dense 3 N d 4 per step does not
         # describe a kernel that touches only the sample's features
@@ -505,15 +514,17 @@ def measure(cfg, input_kind: str, steps: int, warmup: int):
             "map": f"{cfg.rows}x{cfg.cols}", "epochs": cfg.epochs,
             "train_steps_per_pass": cfg.steps,
             "schedule": f"lr {cfg.lr0}->{cfg.lr1} linear, sigma {cfg.sigma0}->{cfg.sigma1} exp",
-            "grid": grid, "block": block, "variant": variant, "input": input_kind,
-            "block_steps": None if sparse else plan["block_steps"],
+            "grid": None if panels else grid, "block": None if panels else block,
+            "variant": variant, "input": input_kind,
+            "block_steps": None if sparse or panels else plan["block_steps"],
         },
         "roofline": roof,
         "bmu_mfma": {
             "achieved": bmu_flops / bmu_s / 1e12, "peak": FP32_MFMA_PEAK_TFLOPS,
             "unit": "TFLOP/s", "frac": bmu_flops / bmu_s / 1e12 / FP32_MFMA_PEAK_TFLOPS,
             "flops": bmu_flops, "ms": bmu_s * 1e3,
-            "note": "som_bmu over all n samples: 2 n N d flops of X W^T (fp32 MFMA) plus "
+            "note": "som_bmu over all n samples: 2 n N d flops of X W^T (fp32 MFMA, or three "
+                    "fp16 products per fp32 one on large calls) plus "
                     "the candidate re-rank, best of 3",
         },
         "train_ms": avg_train_s * 1e3,
