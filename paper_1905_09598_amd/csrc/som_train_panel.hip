@@ -38,6 +38,7 @@
 // and here: 10 x 10 units of 500 floats 1.26 and 0.66, 11 x 11 of 4545 1.54 and
 // 0.89, 30 x 30 of 5000 2.18 and 1.57, 50 x 50 of 10000 6.35 and 3.21, 100 x 100
 // of 2048 4.33 and 2.98.
+#include "som_barrier.h"
 #include "som_device.h"
 
 #include <algorithm>
@@ -997,8 +998,9 @@ __device__ inline bool grid_barrier(const PanelArgs &p, unsigned n, unsigned cha
         __hip_atomic_fetch_add(p.arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
         int out = 0;
-        while (__hip_atomic_load(p.arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
-               n * gridDim.x) {
+        while (!arrivals_reached(__hip_atomic_load(p.arrived, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT),
+                                 n * gridDim.x)) {
             if (__hip_atomic_load(&a.state->order_bad, __ATOMIC_RELAXED,
                                   __HIP_MEMORY_SCOPE_AGENT) != 0)
                 out = 1;
