@@ -844,10 +844,11 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
             } else {
                 // The lowest lane of each row of 16 lanes at the row's minimum
                 // puts its key into LDS, tagged by step, after the position it
-                // stands for (a wave's LDS operations keep their order).  A
-                // wave overwrites its keys of step s - 2 only after it has
-                // read all keys of step s - 1, so after all have read those
-                // of step s - 2.
+                // stands for (a wave's LDS operations keep their order, and the
+                // fences keep the compiler's: position before key here, key
+                // before position where they are read).  A wave overwrites
+                // its keys of step s - 2 only after it has read all keys of
+                // step s - 1, so after all have read those of step s - 2.
                 const int rm = row_min_i32(m);
                 bool win = m == rm && base + mine < a.N;
                 const unsigned long long wins = __ballot(win);
@@ -861,6 +862,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
                                        ((unsigned long long)__float_as_uint(wc) << 32) |
                                            __float_as_uint(wr),
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    __atomic_signal_fence(__ATOMIC_SEQ_CST);
                     __hip_atomic_store(slots + wave * 4 + g,
                                        ((unsigned long long)(unsigned)m << 32) |
                                            (tag << kUnitBits) | (unsigned)unit,
@@ -871,6 +873,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
                 do {
                     v = __hip_atomic_load(slots + (lane & (4 * NW - 1)), __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                    __atomic_signal_fence(__ATOMIC_SEQ_CST);
                     w = __hip_atomic_load(pos + (lane & (4 * NW - 1)), __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_WORKGROUP);
                 } while (__ballot(waits && ((unsigned)(v >> kUnitBits) & 0xffu) != tag) != 0);
