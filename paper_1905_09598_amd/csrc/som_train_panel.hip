@@ -1,9 +1,9 @@
-// Panel training: the online steps of Eq. (1) in panels of M steps, with the
-// pass over the prototypes as two matrix products per panel and the steps
+// Panel training: the online steps of Eq. (1) in panels of M - 1 steps, with
+// the pass over the prototypes as two matrix products per panel and the steps
 // themselves in the space of inner products.
 //
-// Within panel b (steps s0 .. s0 + M - 1, samples x_k, z its first sample)
-// every prototype is w = z + v, and a step with factor h moves v to
+// Within panel b (steps s0 .. s0 + M - 2, samples x_k, z one of them) every
+// prototype is w = z + v, and a step with factor h moves v to
 // (1 - h) v + h e_k, e_k = x_k - z.  With L_l = v . e_l and Q = |v|^2
 //     D_k = |x_k - w|^2 = G_kk - 2 L_k + Q,        G_kl = e_k . e_l,
 //     L_l <- (1 - h) L_l + h G_kl,
@@ -19,17 +19,23 @@
 //     samples (a product over d), both on fp32 matrix instructions in one pass
 //     over the prototypes, held from then on as F_b;
 //   * prepare: panel b + 2's samples gathered, centred and transposed, their
-//     Gram matrix and their products with panel b + 1's samples.
+//     Gram matrix and their products with panel b + 1's samples; and the
+//     distances that panel b + 4's centre is chosen by.
 // The sweep sees F_b where panel b + 1 starts from F_(b+1), so its products
 // are corrected once panel b's coefficients are known (correct): with a_j =
 // x_j - z' the panel's samples in the next panel's centring,
 //     (F_(b+1) - z') . e'_l = beta (F_b - z') . e'_l + sum_j gamma_j a_j . e'_l.
-// Q is carried from panel to panel through the column of the next centre,
-// Q' = Q - 2 v . (z' - z) + |z' - z|^2, and pulled to the sweep's |F_b - z'|^2
-// with weight beta^2, so its rounding does not add up over panels.
+// Q is carried from panel to panel through the column of the next centre, the
+// last of a panel's M, Q' = Q - 2 v . (z' - z) + |z' - z|^2, and pulled to the
+// sweep's |F_b - z'|^2 with weight beta^2, so its rounding does not add up over
+// panels.
 //
-// Centring on a sample of the panel keeps every term at the scale of
-// sample-to-sample distances.
+// Distances are differences of terms at the scale of |x_k - z|^2 and |w - z|^2,
+// so the centre has to lie among the samples: a panel's is, of eight of its
+// samples, the one with the smallest median distance to the others (an outlier
+// of 10,000 times the others' norm as the centre costs every distance of two
+// panels its digits).  That keeps every term at the scale of sample-to-sample
+// distances, as in the pipelined kernels.
 //
 // The exchange between workgroups (1.0-1.2 us) bounds a step of the kernels
 // that hold W across the grid, and the pass over W bounds the streamed ones;
@@ -53,6 +59,21 @@ constexpr int kMaxKSplit = 4;    // column ranges of the pass over the prototype
 constexpr int kGatherDims = 64;  // columns of one gather task
 constexpr int kPrepThreads = 256;
 constexpr int kTPitch = kSub + 4;
+constexpr int kCandidates = 8;   // samples of a panel its centre is chosen from
+constexpr int kPairs = kCandidates * (kCandidates - 1) / 2;
+constexpr int kPairStride = 32;
+
+// Steps of a panel of M columns: the last column is the next centre's.
+template <int M>
+constexpr int panel_steps() {
+    return M - 1;
+}
+// Steps of panel `panel`.
+template <int M>
+__device__ inline int steps_of(const PanelArgs &p, int64_t panel) {
+    const int64_t left = p.t.nsteps - panel * panel_steps<M>();
+    return (int)(left < panel_steps<M>() ? left : panel_steps<M>());
+}
 
 __device__ inline f4 mfma4(const f4 &a, const f4 &b, f4 c) {
 #pragma unroll
@@ -67,8 +88,7 @@ __device__ inline f4 mfma4(const f4 &a, const f4 &b, f4 c) {
 template <int M>
 __device__ inline float panel_coefs(const PanelArgs &p, int64_t panel, int u, int g,
                                     f4 (&gam)[M / 16]) {
-    const int64_t left = p.t.nsteps - panel * M;
-    const int nsub = (int)((left < M ? left : M) + kSub - 1) / kSub;
+    const int nsub = (steps_of<M>(p, panel) + kSub - 1) / kSub;
     const float *pg = p.gam[panel & 1], *pb = p.beta[panel & 1];
     float b[M / 16];
 #pragma unroll
@@ -297,18 +317,53 @@ __device__ inline const float *step_row(const PanelArgs &p, int64_t s) {
     return a.X + (int64_t)(idx >= 0 && idx < a.n ? idx : 0) * a.d;
 }
 
-// Step whose sample is column l of a panel: its steps, but the next panel's
-// first step (its centre) in the place of the panel's own first one, whose
-// column would be zero.
+// Sample row of a panel's candidate c for its centre.
 template <int M>
-__device__ inline int64_t column_step(int64_t panel, int l) {
-    return panel * M + (l == 0 ? M : l);
+__device__ inline const float *candidate_row(const PanelArgs &p, int64_t panel, int c) {
+    return step_row(p, panel * panel_steps<M>() + steps_of<M>(p, panel) * c / kCandidates);
+}
+__device__ inline int pair_index(int i, int j) {  // i < j
+    return i * (2 * kCandidates - 1 - i) / 2 + j - i - 1;
 }
 
-// Floats of one column range's part of a Gram matrix.
+// Centre of a panel: of its candidates the one whose median squared distance to
+// the other seven is smallest (the lowest such).  Every wave finds it for
+// itself, lane l for candidate l % 8.
 template <int M>
-constexpr int gram_stride() {
-    return M * M + 16;
+__device__ inline const float *centre_row(const PanelArgs &p, int64_t panel) {
+    if (panel * panel_steps<M>() >= p.t.nsteps) return step_row(p, p.t.nsteps - 1);
+    const int c = threadIdx.x & (kCandidates - 1);
+    const float *near = p.near[panel & 3];
+    float v[kCandidates - 1];
+#pragma unroll
+    for (int j = 0; j < kCandidates - 1; ++j) {
+        const int o = j + (j >= c ? 1 : 0);  // the j-th other candidate
+        const int at = pair_index(min(c, o), max(c, o));
+        v[j] = 0.f;
+        for (int k = 0; k < p.gsplit; ++k) v[j] += near[k * kPairStride + at];
+    }
+    float median = v[0];
+#pragma unroll
+    for (int j = 0; j < kCandidates - 1; ++j) {
+        int place = 0;
+#pragma unroll
+        for (int k = 0; k < kCandidates - 1; ++k)
+            place += v[k] < v[j] || (v[k] == v[j] && k < j) ? 1 : 0;
+        median = place == (kCandidates - 1) / 2 ? v[j] : median;
+    }
+    unsigned long long key =
+        ((unsigned long long)__float_as_uint(median) << 32) | (unsigned)c;
+#pragma unroll
+    for (int o = 1; o < kCandidates; o *= 2) key = u64_min(key, __shfl_xor(key, o, 64));
+    return candidate_row<M>(p, panel, __builtin_amdgcn_readfirstlane((int)(unsigned)key));
+}
+
+// Sample row of a panel's column l: its steps' samples, then the next panel's
+// centre.
+template <int M>
+__device__ inline const float *column_row(const PanelArgs &p, int64_t panel, int l,
+                                          const float *next_centre) {
+    return l < panel_steps<M>() ? step_row(p, panel * panel_steps<M>() + l) : next_centre;
 }
 
 // Columns c .. c + 3 of a sample row, zero past d.
@@ -326,25 +381,27 @@ __device__ inline f4 row_f4(const PanelArgs &p, const float *x, int c) {
     return v;
 }
 
-// Gather task: columns 64 task .. of a panel: its column set less the centre
-// into ec (row M: the centre), its steps' samples transposed into xt.
+// Gather task: columns 64 task .. of a panel: its columns less the centre into
+// ec (row M: the centre), and raw and transposed into xt (the last one, which is
+// no step, meets a coefficient of zero there).
 template <int M>
 __device__ inline void gather_task(const PanelArgs &p, int64_t panel, int task, float *lds) {
     constexpr int P = kGatherDims + 1;
     const int t = threadIdx.x, c4 = t & 15, r0 = t >> 4;
     const int c = task * kGatherDims + 4 * c4;
     float *xt = p.xt[panel & 3], *ec = p.ec[panel & 1];
-    const f4 z = row_f4(p, step_row(p, panel * M), c);
+    const float *next = centre_row<M>(p, panel + 1);
+    const f4 z = row_f4(p, centre_row<M>(p, panel), c);
     f4 x[M / 16];
 #pragma unroll
     for (int k = 0; k < M / 16; ++k)
-        x[k] = row_f4(p, step_row(p, column_step<M>(panel, r0 + 16 * k)), c);
+        x[k] = row_f4(p, column_row<M>(p, panel, r0 + 16 * k, next), c);
 #pragma unroll
     for (int k = 0; k < M / 16; ++k) {
         const int r = r0 + 16 * k;
         *reinterpret_cast<f4 *>(ec + (int64_t)r * p.dpad + c) = x[k] - z;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) lds[r * P + 4 * c4 + e] = r == 0 ? z[e] : x[k][e];
+        for (int e = 0; e < 4; ++e) lds[r * P + 4 * c4 + e] = x[k][e];
     }
     if (r0 == 0) *reinterpret_cast<f4 *>(ec + (int64_t)M * p.dpad + c) = z;
     __syncthreads();
@@ -358,10 +415,10 @@ __device__ inline void gather_task(const PanelArgs &p, int64_t panel, int task, 
     }
 }
 
-// Gram task: one 16 x 16 tile of products of a panel's column set over column
-// range `part` of p.gsplit.  pair < M/16 (M/16 + 1) / 2: with its own steps
-// e_j, into gm (both tiles of the pair); after that: with panel - 1's samples
-// in this panel's centring, into gx.  Both are [column l][step j].
+// Gram task: one 16 x 16 tile of products of a panel's columns over column
+// range `part` of p.gsplit.  pair < M/16 (M/16 + 1) / 2: with each other, into
+// gm (both tiles of the pair); after that: with panel - 1's samples in this
+// panel's centring, into gx, [column l][step j].
 template <int M>
 __device__ inline void gram_task(const PanelArgs &p, int64_t panel, int pair, int part, f4 *lds) {
     constexpr int NT = M / 16, kOwn = NT * (NT + 1) / 2;
@@ -380,10 +437,13 @@ __device__ inline void gram_task(const PanelArgs &p, int64_t panel, int pair, in
         tj = (pair - kOwn) % NT;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, g = lane >> 4;
-    const int64_t s0 = panel * M;
-    const float *xa = step_row(p, own ? column_step<M>(panel, 16 * ti + i) : s0 - M + 16 * ti + i);
-    const float *xb = step_row(p, column_step<M>(panel, 16 * tj + i));
-    const float *xz = step_row(p, s0);
+    // (a wave-uniform branch around the centre's lane exchange)
+    const float *next = ti == NT - 1 || tj == NT - 1 ? centre_row<M>(p, panel + 1) : nullptr;
+    const float *xz = centre_row<M>(p, panel);
+    const float *xb = column_row<M>(p, panel, 16 * tj + i, next);
+    // (panel - 1 has no step M - 1: this panel's first, at a coefficient of zero)
+    const float *xa = own ? column_row<M>(p, panel, 16 * ti + i, next)
+                          : step_row(p, (panel - 1) * panel_steps<M>() + 16 * ti + i);
     const int tiles = p.dpad / 16;
     const int k0 = (int)((int64_t)tiles * part / p.gsplit);
     const int k1 = (int)((int64_t)tiles * (part + 1) / p.gsplit);
@@ -407,16 +467,10 @@ __device__ inline void gram_task(const PanelArgs &p, int64_t panel, int pair, in
     if (wave > 0) return;
     acc = acc + lds[lane] + lds[64 + lane] + lds[128 + lane];
     // acc[v]: step 16 ti + 4 g + v, column 16 tj + i
-    float *G = (own ? p.gm : p.gx)[panel % 3] + (int64_t)part * gram_stride<M>();
+    float *G = (own ? p.gm : p.gx)[panel % 3] + (int64_t)part * (M * M);
     if (own && ti != tj)
 #pragma unroll
         for (int v = 0; v < 4; ++v) G[(16 * ti + 4 * g + v) * M + 16 * tj + i] = acc[v];
-    // the panel's first step is its centre: no column sees it (the place
-    // holds the next centre, whose norm goes behind the matrix)
-    if (own && ti == 0 && g == 0) {
-        if (tj == 0 && i == 0) G[M * M] = acc[0];
-        acc[0] = 0.f;
-    }
     *reinterpret_cast<f4 *>(G + (16 * tj + i) * M + 16 * ti + 4 * g) = acc;
 }
 
@@ -438,6 +492,47 @@ __device__ inline void prepare_task(const PanelArgs &p, int64_t panel, int task,
 }
 
 constexpr size_t kPrepareLds = 80 * (kGatherDims + 1) * 4;
+
+// Select task: the candidates' squared distances over column range `part`, from
+// direct differences, for centre_row.
+template <int M>
+__device__ inline void select_task(const PanelArgs &p, int64_t panel, int part, float *lds) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const float *x[kCandidates];
+#pragma unroll
+    for (int c = 0; c < kCandidates; ++c) x[c] = candidate_row<M>(p, panel, c);
+    const int quads = p.dpad / 4;
+    const int q0 = (int)((int64_t)quads * part / p.gsplit);
+    const int q1 = (int)((int64_t)quads * (part + 1) / p.gsplit);
+    float acc[kPairs];
+#pragma unroll
+    for (int k = 0; k < kPairs; ++k) acc[k] = 0.f;
+    for (int q = q0 + threadIdx.x; q < q1; q += kPrepThreads) {
+        f4 v[kCandidates];
+#pragma unroll
+        for (int c = 0; c < kCandidates; ++c) v[c] = row_f4(p, x[c], 4 * q);
+        int k = 0;
+#pragma unroll
+        for (int i = 0; i < kCandidates; ++i)
+#pragma unroll
+            for (int j = i + 1; j < kCandidates; ++j, ++k) {
+                const f4 e = v[i] - v[j];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[k] = fmaf(e[c], e[c], acc[k]);
+            }
+    }
+    wave_sums<kPairs>(acc);
+#pragma unroll
+    for (int k = 0; k < kPairs; ++k)
+        if (lane == k) lds[wave * kPairStride + k] = acc[k];
+    __syncthreads();
+    if (threadIdx.x < kPairs) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < kPrepThreads / 64; ++w) s += lds[w * kPairStride + threadIdx.x];
+        p.near[panel & 3][part * kPairStride + threadIdx.x] = s;
+    }
+}
 
 // ----------------------------------------------------------------- correct
 
@@ -476,7 +571,7 @@ __device__ inline void correct_tile(const PanelArgs &p, int64_t panel, int u0) {
                 f4 ga[NT];
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
-                    ga[t] = *reinterpret_cast<const f4 *>(gx + (int64_t)k * gram_stride<M>() +
+                    ga[t] = *reinterpret_cast<const f4 *>(gx + (int64_t)k * (M * M) +
                                                           (16 * t + i) * M + 16 * s + 4 * g);
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
@@ -573,8 +668,7 @@ template <int M, int U, int NW>
 struct ControlLds {
     static constexpr int kUnits = U * NW * 64;
     static constexpr int kGram = 0;
-    static constexpr int kCentre = M * M * 4;                     // M + 16 floats
-    static constexpr int kKeys = kCentre + (M + 16) * 4;          // [2][4 NW]
+    static constexpr int kKeys = M * M * 4;                       // [2][4 NW]
     static constexpr int kWhere = kKeys + 2 * 4 * NW * 8;         // [2][4 NW]
     static constexpr int kBlocks = kWhere + 2 * 4 * NW * 8;       // [M / 16][16][16] fp64
     static constexpr int kTrans = kBlocks + M * kSub * 8;         // 32 units a wave
@@ -605,15 +699,15 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
     const int base = GRID ? (int)blockIdx.x * Lds::kUnits : 0;
     const int mine = (wave * 64 + lane) * U;  // the lane's first unit of the workgroup's
     float *G = reinterpret_cast<float *>(lds + Lds::kGram);
-    float *centre = reinterpret_cast<float *>(lds + Lds::kCentre);
     float *T = reinterpret_cast<float *>(lds + Lds::kTrans) + wave * 32 * kTPitch;
     double *blocks = reinterpret_cast<double *>(lds + Lds::kBlocks);
     unsigned long long *keys = reinterpret_cast<unsigned long long *>(lds + Lds::kKeys);
     unsigned long long *where = reinterpret_cast<unsigned long long *>(lds + Lds::kWhere);
     float *cg = reinterpret_cast<float *>(lds + Lds::kCoef);   // [q][rows][16]
     float *cb = cg + (M / 16 - 1) * rows * kSub;               // [q][rows]
-    const int64_t s0 = panel * M;
-    const int nst = (int)(a.nsteps - s0 < M ? a.nsteps - s0 : M);
+    constexpr int kNext = panel_steps<M>();  // (and the next centre's column)
+    const int64_t s0 = panel * kNext;
+    const int nst = steps_of<M>(p, panel);
     const bool bad = a.state->order_bad != 0;  // used where the BMUs are traced
 
     // The 16 steps' starting products of the lane's units, loaded a sub-block
@@ -626,7 +720,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
                      p.pc + (int64_t)min(base + mine + u, a.N - 1) * M + kSub * sub);
     };
     fetch(0);
-    double Q[U], Lz[U], bsub[U];  // bsub: product of the panel's beta so far
+    double Q[U], lz[U], bsub[U];  // bsub: product of the panel's beta so far
     float row[U], col[U];
     const float rscale = a.topology == 1 ? 0.75f : 1.f;
     const float shift = a.topology == 1 ? 0.5f : 0.f;
@@ -637,6 +731,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
         const int at = min(unit, a.N - 1);
         const double q = p.qc[at];
         Q[u] = unit < a.N ? q : (double)INFINITY;  // a unit past N is never nearest
+        lz[u] = p.pc[(int64_t)at * M + kNext];
         bsub[u] = 1.0;
         int r, c;
         unit_rc(at, a.cols, inv_cols, r, c);
@@ -645,7 +740,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
         col[u] = (float)c + shift * (float)(r & 1);
     }
     {
-        // the Gram matrix; the next centre's row apart, zero in its place
+        // the Gram matrix
         const float *src = p.gm[panel % 3];
         constexpr int kTotal = M * M / 4, kStep = NW * 64, kBatch = 5;
         for (int e0 = threadIdx.x; e0 < kTotal; e0 += kBatch * kStep) {
@@ -657,28 +752,20 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
 #pragma unroll
                 for (int n = 0; n < kBatch; ++n)
                     v[n] = v[n] + reinterpret_cast<const f4 *>(
-                                      src + (int64_t)k * gram_stride<M>())[min(e0 + n * kStep,
+                                      src + (int64_t)k * (M * M))[min(e0 + n * kStep,
                                                                                kTotal - 1)];
 #pragma unroll
             for (int n = 0; n < kBatch; ++n) {
                 const int e = e0 + n * kStep;
-                const f4 zero = {0.f, 0.f, 0.f, 0.f};
-                if (e < M / 4) reinterpret_cast<f4 *>(centre)[e] = v[n];
                 if (e < kTotal) {
-                    const f4 r = e < M / 4 ? zero : v[n];
-                    reinterpret_cast<f4 *>(G)[e] = r;
+                    reinterpret_cast<f4 *>(G)[e] = v[n];
                     const int l = 4 * e / M, c = 4 * e % M;
                     if (l / kSub == c / kSub)
 #pragma unroll
                         for (int x = 0; x < 4; ++x)
-                            blocks[l * kSub + c % kSub + x] = (double)r[x];
+                            blocks[l * kSub + c % kSub + x] = (double)v[n][x];
                 }
             }
-        }
-        if (threadIdx.x == 0) {
-            float zz = src[M * M];
-            for (int k = 1; k < p.gsplit; ++k) zz += src[(int64_t)k * gram_stride<M>() + M * M];
-            centre[M] = zz;
         }
         if (NW > 1 && threadIdx.x < 2 * 4 * NW) keys[threadIdx.x] = 0ull;
     }
@@ -686,7 +773,10 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
         __syncthreads();
     else
         __builtin_amdgcn_wave_barrier();
-    const double zz = (double)centre[M];
+    const double zz = (double)G[kNext * M + kNext];  // |z' - z|^2
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (base + mine + u < a.N) p.qe[base + mine + u] = fma(-2.0, lz[u], Q[u]) + zz;
     PollRegs<4> polls;
 #pragma unroll
     for (int q = 0; q < 4; ++q) polls.v[q] = 0;
@@ -756,16 +846,6 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
 #pragma unroll
                 for (int k = 0; k < kSub; ++k) L[u][k] += (double)own[k];
             }
-        } else {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                // column 0 is the next centre's; the panel's first sample,
-                // its own centre, has none
-                Lz[u] = L[u][0];
-                L[u][0] = 0.0;
-                const int unit = base + mine + u;
-                if (unit < a.N) p.qe[unit] = fma(-2.0, Lz[u], Q[u]) + zz;
-            }
         }
 
         // ---- the steps
@@ -775,14 +855,12 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
 #pragma unroll
             for (int k = 0; k < kSub; ++k) hs[u][k] = 0.f;
         const double *Gs = blocks + sub * kSub * kSub;
-        // lane k holds the k-th step's schedule entry, the Gram entries (k, k)
-        // and (k, k + 1), which the chain of a step needs at once, and the
-        // step's product with the next centre
+        // lane k holds the k-th step's schedule entry and the Gram entries
+        // (k, k) and (k, k + 1), which the chain of a step needs at once
         const int lk = lane & (kSub - 1);
         const float2 sched = fetch_entry(a, s0 + kSub * sub + lk, float2());
         const double diag = Gs[lk * (kSub + 1)];
         const double above = Gs[lk * (kSub + 1) + (lk + 1 < kSub)];
-        const float zcol = sub + lk > 0 ? centre[kSub * sub + lk] : 0.f;
         int trace = 0;
         double grow[kSub];  // the last step's row of the Gram matrix
         double hp[U];
@@ -807,7 +885,6 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
             const int64_t s = s0 + kSub * sub + k;
             const float lr = lane_f(sched.x, k), c2 = lane_f(sched.y, k);
             const double gkk = lane_d(diag, k), gk1 = lane_d(above, k);
-            const double gkz = (double)lane_f(zcol, k);
             // The distances as integers: positive ones in order, negative ones
             // (the rounding of a distance near zero) below them, a NaN as inf.
             double D[U];
@@ -898,12 +975,13 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
                 Q[u] = fma(hd, fma(hd, D[u], -D[u]) + (gkk - Q[u]), Q[u]);
                 if constexpr (k + 1 < kSub)
                     L[u][k + 1] = fma(hd, gk1 - L[u][k + 1], L[u][k + 1]);
-                Lz[u] = fma(hd, gkz - Lz[u], Lz[u]);
                 hp[u] = hd;
             }
             return true;
         });
         if (GRID && !ok) return false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) lz[u] = L[u][kSub - 1];  // at last the next centre's
         if (blockIdx.x == 0 && wave == 0 && a.bmu_trace && !bad && lane < kSub &&
             kSub * sub + lane < nst)
             a.bmu_trace[s0 + kSub * sub + lane] = trace;
@@ -942,30 +1020,43 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        if (base + mine + u < a.N) p.qn[base + mine + u] = fma(-2.0, Lz[u], Q[u]) + zz;
+        if (base + mine + u < a.N) p.qn[base + mine + u] = fma(-2.0, lz[u], Q[u]) + zz;
     return true;
 }
 
 // ----------------------------------------------------------------- kernels
 
-// Work of a launch beside the control: sweep tasks of `panel` first, then the
-// preparation of panel `prep` (and the one after it with two_preps).
+// Work of a launch beside the control: the sweep of `panel`, then the
+// preparation of `nprep` panels from `prep` on, then the distances for the
+// centres of the panels from `sel` on.
+struct SideWork {
+    int64_t panel, prep, sel;
+    int nsweep, nprep, nsel, apply, prod;
+};
 template <int M, int TU, int BW>
-__device__ inline void side_task(const PanelArgs &p, int64_t panel, int t, int nsweep, bool apply,
-                                 bool prod, int64_t prep, unsigned char *smem) {
-    if (t < nsweep)
-        sweep<M, TU, BW>(p, panel, t, apply, prod, smem);
-    else if (threadIdx.x < kPrepThreads)
-        prepare_task<M>(p, prep + (t - nsweep) / p.prep, (t - nsweep) % p.prep,
-                        reinterpret_cast<float *>(smem));
+__device__ inline void side_task(const PanelArgs &p, const SideWork &w, int t,
+                                 unsigned char *smem) {
+    float *lds = reinterpret_cast<float *>(smem);
+    if (t < w.nsweep) {
+        sweep<M, TU, BW>(p, w.panel, t, w.apply, w.prod, smem);
+    } else if (threadIdx.x < kPrepThreads) {
+        t -= w.nsweep;
+        if (t < w.nprep * p.prep)
+            prepare_task<M>(p, w.prep + t / p.prep, t % p.prep, lds);
+        else
+            select_task<M>(p, w.sel + (t - w.nprep * p.prep) / p.gsplit,
+                           (t - w.nprep * p.prep) % p.gsplit, lds);
+    }
+}
+// Tasks of a launch.
+int side_tasks(const PanelArgs &p, const SideWork &w) {
+    return w.nsweep + w.nprep * p.prep + w.nsel * p.gsplit;
 }
 
 template <int M, int TU, int BW>
-__global__ __launch_bounds__(64 * BW, 2) void panel_side_kernel(PanelArgs p, int64_t panel,
-                                                               int nsweep, int apply, int prod,
-                                                               int64_t prep) {
+__global__ __launch_bounds__(64 * BW, 2) void panel_side_kernel(PanelArgs p, SideWork w) {
     extern __shared__ __align__(16) unsigned char smem[];
-    side_task<M, TU, BW>(p, panel, blockIdx.x, nsweep, apply, prod, prep, smem);
+    side_task<M, TU, BW>(p, w, blockIdx.x, smem);
 }
 
 template <int M>
@@ -976,11 +1067,11 @@ __global__ __launch_bounds__(64) void panel_correct_kernel(PanelArgs p, int64_t 
 // One panel on one control workgroup (workgroup 0), the others beside it.
 // With few units the control workgroup corrects their products itself.
 template <int M, int U, int NW, int TU>
-__global__ __launch_bounds__(64 * NW, 2) void panel_step_kernel(PanelArgs p, int64_t panel,
-                                                               int nsweep, int apply, int prod) {
+__global__ __launch_bounds__(64 * NW, 2) void panel_step_kernel(PanelArgs p, SideWork w) {
     extern __shared__ __align__(16) unsigned char smem[];
+    const int64_t panel = w.panel;
     if (blockIdx.x > 0) {
-        side_task<M, TU, NW>(p, panel, (int)blockIdx.x - 1, nsweep, apply, prod, panel + 2, smem);
+        side_task<M, TU, NW>(p, w, (int)blockIdx.x - 1, smem);
         return;
     }
     if (!p.correct) {
@@ -1065,6 +1156,13 @@ __device__ __attribute__((noinline)) void grid_prepare(uint64_t args, uint32_t l
     prepare_task<M>(p, uniform64(panel), __builtin_amdgcn_readfirstlane(t),
                     reinterpret_cast<float *>(lds_at(lds)));
 }
+template <int M>
+__device__ __attribute__((noinline)) void grid_select(uint64_t args, uint32_t lds, int64_t panel,
+                                                    int part) {
+    const PanelArgs &p = segment_args(args);
+    select_task<M>(p, uniform64(panel), __builtin_amdgcn_readfirstlane(part),
+                   reinterpret_cast<float *>(lds_at(lds)));
+}
 template <int M, int U>
 __device__ __attribute__((noinline)) void grid_correct(uint64_t args, int64_t panel) {
     const PanelArgs &p = segment_args(args);
@@ -1091,9 +1189,14 @@ __global__ __launch_bounds__(256, 2) void panel_grid_kernel(PanelArgs p) {
     const uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
     const int C = p.controllers, b = blockIdx.x, others = (int)gridDim.x - C;
     if (b < C && b >= C - p.absent) return;
-    const int64_t panels = (a.nsteps + M - 1) / M;
+    const int64_t panels = (a.nsteps + panel_steps<M>() - 1) / panel_steps<M>();
     const int nsweep = (a.N + 16 * TU - 1) / (16 * TU) * p.ksplit;
     unsigned n = 0;
+    for (int t = b; t < (panels < 4 ? (int)panels : 4) * p.gsplit; t += gridDim.x) {
+        grid_select<M>(args, lds, t / p.gsplit, t % p.gsplit);
+        __syncthreads();
+    }
+    if (!grid_barrier(p, ++n, smem)) return;
     for (int t = b; t < 2 * p.prep; t += gridDim.x) {
         grid_prepare<M>(args, lds, t / p.prep, t % p.prep);
         __syncthreads();
@@ -1111,8 +1214,11 @@ __global__ __launch_bounds__(256, 2) void panel_grid_kernel(PanelArgs p) {
         } else {
             const bool prod = k + 1 < panels;
             const int ns = k > 0 || prod ? nsweep : 0, np = k + 2 < panels ? p.prep : 0;
-            for (int t = b - C; t < ns + np; t += others) {
-                if (t >= ns)
+            const int nc = k + 4 < panels ? p.gsplit : 0;
+            for (int t = b - C; t < ns + np + nc; t += others) {
+                if (t >= ns + np)
+                    grid_select<M>(args, lds, k + 4, t - ns - np);
+                else if (t >= ns)
                     grid_prepare<M>(args, lds, k + 2, t - ns);
                 else if (k == 0)
                     grid_sweep<M, TU, false, true>(args, lds, k, t);
@@ -1136,8 +1242,8 @@ struct PanelInstance {
     int m, u, nw, tu;
     bool grid;
     size_t (*lds)(int rows);
-    void (*step)(PanelArgs, int64_t, int, int, int);
-    void (*side)(PanelArgs, int64_t, int, int, int, int64_t);
+    void (*step)(PanelArgs, SideWork);
+    void (*side)(PanelArgs, SideWork);
     void (*correct)(PanelArgs, int64_t);
     void (*whole)(PanelArgs);
 };
@@ -1200,7 +1306,7 @@ bool plan_train_panel(int32_t N, int32_t d, int num_cus, int max_lds, PanelPlan 
                 return false;
             const int64_t most = (int64_t)std::min(per_cu, 2) * num_cus;
             if (wgs + 32 > most) continue;
-            plan->grid = (int32_t)std::min<int64_t>(most, wgs + ug * plan->ksplit + plan->prep);
+            plan->grid = (int32_t)std::min<int64_t>(most, wgs + ug * plan->ksplit + plan->prep + plan->gsplit);
         }
         plan->instance = k;
         plan->m = in.m;
@@ -1246,7 +1352,7 @@ int64_t panel_floats(const PanelPlan &pl, PanelArgs *p, float *base) {
         *at = p ? reinterpret_cast<std::remove_reference_t<decltype(**at)> *>(base + off) : nullptr;
         off += (count * (int64_t)(sizeof(**at) / sizeof(float)) + 63) & ~(int64_t)63;
     };
-    const int64_t gram = (int64_t)pl.gsplit * (pl.m * pl.m + 16);
+    const int64_t gram = (int64_t)pl.gsplit * pl.m * pl.m;
     for (int k = 0; k < 2; ++k) {
         take(&a.ec[k], (int64_t)(pl.m + 1) * pl.dpad);
         take(&a.prod[k], (int64_t)pl.ksplit * pl.npad * pl.m);
@@ -1258,7 +1364,10 @@ int64_t panel_floats(const PanelPlan &pl, PanelArgs *p, float *base) {
         take(&a.gm[k], gram);
         take(&a.gx[k], gram);
     }
-    for (int k = 0; k < 4; ++k) take(&a.xt[k], (int64_t)pl.dpad * pl.m);
+    for (int k = 0; k < 4; ++k) {
+        take(&a.xt[k], (int64_t)pl.dpad * pl.m);
+        take(&a.near[k], (int64_t)pl.gsplit * kPairStride);
+    }
     take(&a.pc, (int64_t)pl.npad * pl.m);
     take(&a.qc, (int64_t)pl.npad);
     take(&a.qn, (int64_t)pl.npad);
@@ -1289,22 +1398,44 @@ hipError_t launch_train_panel(const PanelArgs &args, const PanelPlan &pl, hipStr
         return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(in.whole), dim3(pl.grid),
                                           dim3(256), params, (unsigned)pl.lds, s);
     }
-    const int64_t panels = (p.t.nsteps + pl.m - 1) / pl.m;
+    const int64_t panels = (p.t.nsteps + pl.m - 2) / (pl.m - 1);
     const int nsweep = (p.t.N + 16 * in.tu - 1) / (16 * in.tu) * pl.ksplit;
     const dim3 block(64 * in.nw);
     const size_t side_lds = in.lds(0);
     p.correct = p.t.N > kSelfCorrect;
-    in.side<<<dim3(2 * pl.prep), block, side_lds, s>>>(p, 0, 0, 0, 0, 0);
-    in.side<<<dim3(nsweep), block, side_lds, s>>>(p, -1, nsweep, 0, 1, 0);
+    const auto side = [&](const SideWork &w) {
+        in.side<<<dim3(side_tasks(p, w)), block, side_lds, s>>>(p, w);
+    };
+    SideWork w{};
+    w.nsel = (int)std::min<int64_t>(panels, 4);
+    side(w);
+    w = SideWork{};
+    w.nprep = 2;
+    side(w);
+    w = SideWork{};
+    w.panel = -1;
+    w.nsweep = nsweep;
+    w.prod = 1;
+    side(w);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     for (int64_t b = 0; b < panels; ++b) {
-        const int apply = b > 0, prod = b + 1 < panels;
-        const int ns = apply || prod ? nsweep : 0, np = b + 2 < panels ? pl.prep : 0;
+        w.panel = b;
+        w.prep = b + 2;
+        w.sel = b + 4;
+        w.apply = b > 0;
+        w.prod = b + 1 < panels;
+        w.nsweep = w.apply || w.prod ? nsweep : 0;
+        w.nprep = b + 2 < panels;
+        w.nsel = b + 4 < panels;
         if (p.correct) in.correct<<<dim3((p.t.N + 15) / 16), dim3(64), 0, s>>>(p, b);
-        in.step<<<dim3(1 + ns + np), block, pl.lds, s>>>(p, b, ns, apply, prod);
+        in.step<<<dim3(1 + side_tasks(p, w)), block, pl.lds, s>>>(p, w);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    in.side<<<dim3(nsweep), block, side_lds, s>>>(p, panels, nsweep, 1, 0, 0);
+    w = SideWork{};
+    w.panel = panels;
+    w.nsweep = nsweep;
+    w.apply = 1;
+    side(w);
     return hipGetLastError();
 }
 
