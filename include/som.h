@@ -142,8 +142,9 @@ som_status som_set_stream(som_map *map, void *stream);
 /* Online training (paper Sec. 5A and 6C): epochs * n steps over the n x d
  * row-major fp32 device matrix X, the whole per-sample loop on the device.
  * Stream-ordered.  Calls train in panels of 48 to 80 steps where that is the
- * faster way (maps of up to 32,768 units; not short calls, and not maps of
- * more than 700 units whose rows fit in LDS few to a workgroup): the steps run
+ * faster way (maps of up to 16,384 units, beyond 2,560 units rows of up to 3,072
+ * floats; not short calls, and not maps of more than 700 units whose rows fit in
+ * LDS few to a workgroup): the steps run
  * on inner products while the prototypes are read and written once a panel
  * (one launch or two per panel up to 1,024 units, one cooperative kernel for
  * the call beyond), with up to about 16 N M + 8 M d floats of work memory (M

@@ -713,14 +713,14 @@ static bool panels_requested() {
 }
 
 // Training in panels (som_train_panel.hip) when no launch shape was asked for,
-// the persistent kernel would take longer and the build has a panel
-// shape whose buffers fit the cap; *done tells.
+// persistent_train_first does not keep the call and the build has a panel shape
+// whose buffers fit the cap; *done tells.
 static som_status train_panels(som_map *m, const som_schedule *s, som::TrainArgs &a,
                                const som::TrainPlan &persistent, int64_t nsteps, int64_t total,
                                bool *done) {
     *done = false;
     if (a.grid || a.variant || a.block_m || a.sweepers || a.lds_rows >= 0) return SOM_OK;
-    if (!panels_requested() && som::persistent_train_faster(m->N, m->d, nsteps, persistent))
+    if (!panels_requested() && som::persistent_train_first(m->N, m->d, nsteps, persistent))
         return SOM_OK;
     int max_lds = 0;
     hipError_t e = hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock,

@@ -136,8 +136,9 @@ struct PanelArgs {
 };
 // The panel shape for N units of d floats; false when the build has none.
 bool plan_train_panel(int32_t N, int32_t d, int num_cus, int max_lds, PanelPlan *plan);
-// True where the persistent kernel of that plan takes less time than panels.
-bool persistent_train_faster(int32_t N, int32_t d, int64_t nsteps, const TrainPlan &plan);
+// True where the persistent kernel of that plan takes less time than panels, or
+// distances of more digits.
+bool persistent_train_first(int32_t N, int32_t d, int64_t nsteps, const TrainPlan &plan);
 // Floats of a plan's buffers; with p, also sets its pointers from base.
 int64_t panel_floats(const PanelPlan &plan, PanelArgs *p, float *base);
 hipError_t launch_train_panel(const PanelArgs &a, const PanelPlan &plan, hipStream_t s);

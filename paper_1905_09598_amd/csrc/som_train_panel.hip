@@ -35,7 +35,8 @@
 // samples, the one with the smallest median distance to the others (an outlier
 // of 10,000 times the others' norm as the centre costs every distance of two
 // panels its digits).  That keeps every term at the scale of sample-to-sample
-// distances, as in the pipelined kernels.
+// distances, as in the pipelined kernels; the blocked kernel's distances are
+// direct differences, and its calls stay on it (persistent_train_first).
 //
 // The exchange between workgroups (1.0-1.2 us) bounds a step of the kernels
 // that hold W across the grid, and the pass over W bounds the streamed ones;
@@ -1267,7 +1268,7 @@ constexpr PanelInstance exchanging() {
 
 const PanelInstance kPanels[] = {
     one_workgroup<80, 1, 4, 1>(), one_workgroup<64, 1, 8, 1>(), one_workgroup<48, 2, 8, 2>(),
-    one_workgroup<32, 2, 8, 2>(), exchanging<80, 1, 2>(),       exchanging<80, 2, 2>(),
+    one_workgroup<32, 2, 8, 2>(), exchanging<80, 1, 2>(),
 };
 
 // Up to this many units the control workgroup corrects the products itself;
@@ -1329,14 +1330,22 @@ bool plan_train_panel(int32_t N, int32_t d, int num_cus, int max_lds, PanelPlan 
 // longest rows of its instances for short samples) 2.07 and 2.58, 1024 of 4608
 // 2.30 and 1.64; up to 512 floats 40 rows a workgroup (10000 of 512) 2.33 and
 // 2.46, 46 rows (11664 of 512) 2.66 and 2.48; longer rows 25 a workgroup (6400
-// of 1024) 2.29 and 2.55, 32 rows (8100 of 1024) 2.85 and 2.57.  The other
-// kernels lose at every size measured: 4900 of 1536, streamed, 3.04 and 2.56.
+// of 1024) 2.29 and 2.55, 32 rows (8100 of 1024) 2.85 and 2.57.  The streamed
+// pipelined kernel loses at every size measured: 4900 of 1536 3.04 and 2.56.
 // Short calls pay for the panels' preparation, the first pass and the last.
 // Microseconds per call: 10000 units of 2048, 80 steps 422 and 445, 160 steps
 // 761 and 674; 2500 of 5000, 80 steps 383 and 384; 900 of 5000, 20 steps 90 and
 // 97, 40 steps 132 and 119; 400 of 2000, 2 steps 49 and 51, 5 steps 54 and 50;
 // 100 of 500, 1 step 45 and 38.
-bool persistent_train_faster(int32_t N, int32_t d, int64_t nsteps, const TrainPlan &plan) {
+//
+// The blocked kernel (maps of more than 64 units a workgroup, and beyond 2,560
+// units rows of more than 3,072 floats) always stays: its distances are direct
+// differences x - w, which keep more digits where many units lie close together.
+// Relative root mean square error of the smallest distance over 20,000 uniform
+// prototypes, that kernel and panels (emulated in fp32): d = 3 3e-8 and 2e-4, d = 8
+// 5e-8 and 3e-6, d = 64 1e-7 and 4e-7.
+bool persistent_train_first(int32_t N, int32_t d, int64_t nsteps, const TrainPlan &plan) {
+    if (plan.variant < 2) return true;
     if (nsteps < (N > 1024 ? 96 : d > 2048 ? 40 : d > 1024 ? 4 : 1)) return true;
     constexpr int kOneWorkgroup = 700, kRowLength = 3072;
     const int rows = d <= 512 ? 40 : 28;
