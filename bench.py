@@ -462,10 +462,9 @@ def measure(cfg, input_kind: str, steps: int, warmup: int):
     # the LDS-resident kernels keep W on chip and wait on the grid exchange;
     # the streamed ones read and write W once per block of steps
     bound = "hbm" if plan["variant"] in (0, 2, 4) else "latency"
-    # every workload of the table trains in panels unless a launch shape is
-    # forced: their steps wait on each other through LDS, or on the exchange
+    # the steps of a panel wait on each other through LDS, or on the exchange
     # between the control workgroups beyond 1,024 units
-    panels = not sparse and not any(k.startswith("SOM_TRAIN_") for k in os.environ)
+    panels = not sparse and m.train_route(cfg.steps) == "panels"
     if panels:
         kernel_name = "panel_step_kernel" if cfg.units <= 1024 else "panel_grid_kernel"
         variant, bound, traffic = "panels", "latency", None

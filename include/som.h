@@ -355,6 +355,15 @@ som_status som_suggest_size(int64_t m, double lambda1, double lambda2, int32_t *
  * Errors: as som_pca2. */
 som_status som_init_linear(som_map *map, const float *X, int64_t n);
 
+/* How som_train would run a call of nsteps steps on this map, and som_bmu,
+ * som_bmu2, som_evaluate and the batch map a search of n samples (an
+ * allocation that fails then can still lead to the persistent kernel or to the
+ * fp32 products). */
+enum { SOM_TRAIN_PERSISTENT = 0, SOM_TRAIN_PANELS = 1 };
+enum { SOM_BMU_DIRECT = 0, SOM_BMU_FP32 = 1, SOM_BMU_HALVES = 2 };
+som_status som_train_route(const som_map *map, int64_t nsteps, int32_t *route);
+som_status som_bmu_route(const som_map *map, int64_t n, int32_t *route);
+
 /* Launch shape of som_train's persistent kernel for this map (the path of
  * calls that do not train in panels, see som_train): workgroups, threads
  * per workgroup, kernel variant (0 = prototypes streamed from memory once

@@ -28,7 +28,7 @@ __all__ = [
     "som_quantization_error", "som_topographic_error", "som_get_weights", "som_set_weights",
     "som_synchronize", "som_get_shape", "som_shuffle", "som_train_plan",
     "som_pca2", "som_suggest_size", "som_init_linear", "som_evaluate", "som_stream_inplace",
-    "som_bmu2_noalloc", "som_status_string", "RECT", "HEX", "LINEAR", "EXPONENTIAL", "EXPORTED",
+    "som_bmu2_noalloc", "som_status_string", "som_train_route", "som_bmu_route", "RECT", "HEX", "LINEAR", "EXPONENTIAL", "EXPORTED",
 ]
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -48,7 +48,7 @@ EXPORTED = (
     "som_topographic_error", "som_get_weights", "som_set_weights",
     "som_synchronize", "som_get_shape", "som_shuffle", "som_train_plan",
     "som_pca2", "som_suggest_size", "som_init_linear", "som_evaluate", "som_stream_inplace",
-    "som_bmu2_noalloc", "som_status_string",
+    "som_bmu2_noalloc", "som_status_string", "som_train_route", "som_bmu_route",
 )
 
 
@@ -111,6 +111,8 @@ def lib():
                           C.POINTER(i32)],
         "som_shuffle": [u64, i64, i64, vp],
         "som_train_plan": [vp, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)],
+        "som_train_route": [vp, i64, C.POINTER(i32)],
+        "som_bmu_route": [vp, i64, C.POINTER(i32)],
         "som_pca2": [vp, i64, i32, vp, C.POINTER(C.c_double), vp, vp, vp],
         "som_suggest_size": [i64, C.c_double, C.c_double, C.POINTER(i32), C.POINTER(i32),
                              C.POINTER(i64)],
@@ -254,6 +256,18 @@ def som_shuffle(seed: int, epoch: int, n: int):
     out = np.empty(n, dtype=np.int32)
     _check(lib().som_shuffle(C.c_uint64(seed), epoch, n, out.ctypes.data), "som_shuffle")
     return out
+
+
+def som_train_route(handle: int, nsteps: int) -> str:
+    r = C.c_int32()
+    _check(lib().som_train_route(handle, nsteps, C.byref(r)), "som_train_route")
+    return ("persistent", "panels")[r.value]
+
+
+def som_bmu_route(handle: int, n: int) -> str:
+    r = C.c_int32()
+    _check(lib().som_bmu_route(handle, n, C.byref(r)), "som_bmu_route")
+    return ("direct", "fp32", "halves")[r.value]
 
 
 def som_train_plan(handle: int):
@@ -460,6 +474,14 @@ class Map:
 
     def plan(self) -> dict:
         return som_train_plan(self.handle)
+
+    def train_route(self, nsteps: int) -> str:
+        """How a training of nsteps steps runs: "persistent" or "panels"."""
+        return som_train_route(self.handle, nsteps)
+
+    def bmu_route(self, n: int) -> str:
+        """How a search of n samples runs: "direct", "fp32" or "halves"."""
+        return som_bmu_route(self.handle, n)
 
     def init_linear(self, X) -> None:
         """Prototypes on the plane of X's two largest principal components."""

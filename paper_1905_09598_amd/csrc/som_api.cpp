@@ -282,19 +282,41 @@ som_status run_eval_half(som_map *m, som::EvalArgs a, const som::HalfPlan &h, in
     return from_hip(e);
 }
 
+// The route of a search of n samples, with its plan in *a and *half; -1 when
+// no route's scratch fits the cap.  SOM_BMU_ROUTE=1 / 2 asks for the fp32
+// products / the halves (tests and sweeps).
+int plan_search(const som_map *m, int64_t n, som::EvalArgs *a, som::HalfPlan *half) {
+    *a = som::EvalArgs{};
+    a->W = m->W;
+    a->ld = m->ld;
+    a->N = m->N;
+    a->d = m->d;
+    a->rows = m->rows;
+    a->cols = m->cols;
+    a->topology = m->topology;
+    a->n = n;
+    const char *r = getenv("SOM_BMU_ROUTE");
+    const int asked = r && (r[0] == '1' || r[0] == '2') && r[1] == '\0' ? r[0] - '0' : -1;
+    if (asked < 0 && som::bmu_few(*a) && (uint64_t)n * m->N * sizeof(float) <= max_bytes())
+        return SOM_BMU_DIRECT;
+    double fp32_us = 0.0;
+    const bool fp32 = som::plan_bmu_candidates(a, m->num_cus, max_bytes(), &fp32_us);
+    if (!fp32) return -1;
+    if (asked != SOM_BMU_FP32 &&
+        som::plan_bmu_half(a, m->num_cus, max_bytes(),
+                           asked == SOM_BMU_HALVES ? (double)INFINITY : fp32_us, half))
+        return SOM_BMU_HALVES;
+    return SOM_BMU_FP32;
+}
+
 som_status run_eval(som_map *m, const float *X, int64_t n, int32_t *idx1,
                     int32_t *idx2, float *d1) {
-    som::EvalArgs a{};
-    a.W = m->W;
-    a.ld = m->ld;
-    a.N = m->N;
-    a.d = m->d;
-    a.rows = m->rows;
-    a.cols = m->cols;
-    a.topology = m->topology;
+    som::EvalArgs a;
+    som::HalfPlan half;
+    const int route = plan_search(m, n, &a, &half);
+    if (route < 0) return SOM_E_OOM;
     a.X = X;
-    a.n = n;
-    if (som::bmu_few(a) && (uint64_t)n * m->N * sizeof(float) <= max_bytes()) {
+    if (route == SOM_BMU_DIRECT) {
         const som_status st = ensure_eval_scratch(m, n, 0, n * m->N);
         if (st != SOM_OK) return st;
         a.idx1 = idx1;
@@ -303,11 +325,7 @@ som_status run_eval(som_map *m, const float *X, int64_t n, int32_t *idx1,
         a.x_vec4 = (m->d % 4 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0);
         return from_hip(som::launch_bmu_few(a, m->part, m->stream));
     }
-    double fp32_us = 0.0;
-    if (!som::plan_bmu_candidates(&a, m->num_cus, max_bytes(), &fp32_us)) return SOM_E_OOM;
-    som::HalfPlan half;
-    if (som::plan_bmu_half(&a, m->num_cus, max_bytes(), fp32_us, &half))
-        return run_eval_half(m, a, half, idx1, idx2, d1);
+    if (route == SOM_BMU_HALVES) return run_eval_half(m, a, half, idx1, idx2, d1);
     som_status st = ensure_eval_scratch(m, n, som::bmu_cand_ints(a), som::bmu_part_floats(a));
     if (st != SOM_OK) return st;
     a.wnorm = m->wnorm;
@@ -596,6 +614,31 @@ som_status som_init_linear(som_map *m, const float *X, int64_t n) {
     return check_deferred(m);
 }
 
+static bool plan_panels(const som_map *m, const som::TrainArgs &a, const som::TrainPlan &persistent,
+                        int64_t nsteps, som::PanelPlan *plan);
+
+som_status som_train_route(const som_map *m, int64_t nsteps, int32_t *route) {
+    if (!m || nsteps <= 0 || !route) return SOM_E_ARG;
+    const som::TrainArgs a = train_args(const_cast<som_map *>(m), nullptr, 1);
+    som::TrainPlan p;
+    const hipError_t e = som::plan_train(a, m->num_cus, &p);
+    if (e == hipErrorInvalidValue) return SOM_E_UNSUPPORTED;
+    if (e != hipSuccess) return from_hip(e);
+    som::PanelPlan panels;
+    *route = plan_panels(m, a, p, nsteps, &panels) ? SOM_TRAIN_PANELS : SOM_TRAIN_PERSISTENT;
+    return SOM_OK;
+}
+
+som_status som_bmu_route(const som_map *m, int64_t n, int32_t *route) {
+    if (!m || n <= 0 || n > INT32_MAX || !route) return SOM_E_ARG;
+    som::EvalArgs a;
+    som::HalfPlan half;
+    const int r = plan_search(m, n, &a, &half);
+    if (r < 0) return SOM_E_OOM;
+    *route = r;
+    return SOM_OK;
+}
+
 som_status som_train_plan(const som_map *m, int32_t *grid, int32_t *block,
                           int32_t *variant, int32_t *block_steps) {
     if (!m) return SOM_E_ARG;
@@ -712,25 +755,31 @@ static bool panels_requested() {
     return v && v[0] == '6' && v[1] == '\0';
 }
 
-// Training in panels (som_train_panel.hip) when no launch shape was asked for,
-// persistent_train_first does not keep the call and the build has a panel shape
-// whose buffers fit the cap; *done tells.
+// Whether a call trains in panels (som_train_panel.hip): no launch shape was
+// asked for, persistent_train_first does not keep the call, and the build has a
+// panel shape whose buffers fit the cap.
+static bool plan_panels(const som_map *m, const som::TrainArgs &a, const som::TrainPlan &persistent,
+                        int64_t nsteps, som::PanelPlan *plan) {
+    if (a.grid || a.variant || a.block_m || a.sweepers || a.lds_rows >= 0) return false;
+    if (!panels_requested() && som::persistent_train_first(m->N, m->d, nsteps, persistent))
+        return false;
+    int max_lds = 0;
+    if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, m->device) !=
+        hipSuccess)
+        return false;
+    return som::plan_train_panel(m->N, m->d, m->num_cus, max_lds, plan) &&
+           (uint64_t)som::panel_floats(*plan, nullptr, nullptr) * sizeof(float) <= max_bytes();
+}
+
+// A training call in panels where plan_panels says so; *done tells.
 static som_status train_panels(som_map *m, const som_schedule *s, som::TrainArgs &a,
                                const som::TrainPlan &persistent, int64_t nsteps, int64_t total,
                                bool *done) {
     *done = false;
-    if (a.grid || a.variant || a.block_m || a.sweepers || a.lds_rows >= 0) return SOM_OK;
-    if (!panels_requested() && som::persistent_train_first(m->N, m->d, nsteps, persistent))
-        return SOM_OK;
-    int max_lds = 0;
-    hipError_t e = hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock,
-                                         m->device);
-    if (e != hipSuccess) return from_hip(e);
     som::PanelPlan plan;
-    if (!som::plan_train_panel(m->N, m->d, m->num_cus, max_lds, &plan)) return SOM_OK;
+    if (!plan_panels(m, a, persistent, nsteps, &plan)) return SOM_OK;
     const int64_t floats = som::panel_floats(plan, nullptr, nullptr);
-    if ((uint64_t)floats * sizeof(float) > max_bytes()) return SOM_OK;
-    e = stage_steps(m, s, a.n, nsteps, total, a);
+    hipError_t e = stage_steps(m, s, a.n, nsteps, total, a);
     if (e == hipSuccess) e = ensure(m, &m->panel, &m->panel_cap, floats);
     if (e != hipSuccess) return from_hip(e);
     a.grid = plan.controllers;

@@ -308,7 +308,8 @@ bool plan_bmu_half(EvalArgs *a, int num_cus, uint64_t max_bytes, double fp32_us,
     // row: microseconds with the fp32 products and with halves, 9 samples of
     // 12000 on 25 units 50 and 159, 1500 of 2000 on 400 units 56 and 64; 1307 of
     // 186 on 5200 units 120 and 90.
-    if (a->n * (int64_t)a->N < (int64_t)1 << 20) return false;
+    const bool asked = isinf(fp32_us);
+    if (!asked && a->n * (int64_t)a->N < (int64_t)1 << 20) return false;
     const int64_t slabs = ceil_div(a->d, kHK), tiles_u = ceil_div(a->N, kHN);
     const int64_t row_bytes = slabs * kHK * 4;
     if ((uint64_t)half_rows_halves(a->N, a->d, kHN) * 2 > max_bytes) return false;

@@ -199,7 +199,8 @@ struct HalfPlan {
     int64_t chunk = 0;
     int32_t splits = 1, split_len = 0, ugroups = 0, group_units = 0, slabs = 0;
 };
-// True (and *plan set) when that is expected to take less than fp32_us.
+// True (and *plan set) when that is expected to take less than fp32_us (infinity:
+// wherever its scratch fits the cap).
 bool plan_bmu_half(EvalArgs *a, int num_cus, uint64_t max_bytes, double fp32_us, HalfPlan *plan);
 // Halves that `rows` rows take, stored in whole tiles of `tile` rows.
 int64_t half_rows_halves(int64_t rows, int32_t d, int tile);
