@@ -65,7 +65,7 @@ struct som_map {
     float *part = nullptr;
     int64_t part_cap = 0;
     // the search's rows in halves: samples (one chunk) and prototypes, with
-    // their scales; w_bad follows the prototypes' scales
+    // their scales; the flags of rows without halves follow the prototypes' scales
     void *xhalf = nullptr, *whalf = nullptr;
     float *xscale = nullptr, *wscale = nullptr;
     int64_t xhalf_cap = 0, whalf_cap = 0, xscale_cap = 0, wscale_cap = 0;
@@ -251,7 +251,7 @@ som_status run_eval_half(som_map *m, som::EvalArgs a, const som::HalfPlan &h, in
     hipError_t e = ensure(m, reinterpret_cast<_Float16 **>(&m->xhalf), &m->xhalf_cap, xh);
     if (e == hipSuccess) e = ensure(m, reinterpret_cast<_Float16 **>(&m->whalf), &m->whalf_cap, wh);
     if (e == hipSuccess) e = ensure(m, &m->xscale, &m->xscale_cap, rows);
-    if (e == hipSuccess) e = ensure(m, &m->wscale, &m->wscale_cap, (int64_t)a.N + 1);
+    if (e == hipSuccess) e = ensure(m, &m->wscale, &m->wscale_cap, (int64_t)a.N + 2);
     if (e != hipSuccess) return from_hip(e);
     a.wnorm = m->wnorm;
     a.cand = m->cand;
@@ -261,12 +261,12 @@ som_status run_eval_half(som_map *m, som::EvalArgs a, const som::HalfPlan &h, in
     a.xscale = m->xscale;
     a.wscale = m->wscale;
     int32_t *bad = reinterpret_cast<int32_t *>(m->wscale + a.N);
-    a.w_bad = bad;
+    a.bad = bad;
     a.x_vec4 = (m->d % 4 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0);
     e = som::launch_row_sqnorm(m->W, m->ld, m->N, m->wnorm, bad, m->stream);
     if (e == hipSuccess)
         e = som::launch_split_rows(m->W, a.N, m->ld, a.d, som::kHalfUnits, m->whalf, m->wscale, bad,
-                                   m->stream);
+                                   true, m->stream);
     for (int64_t at = 0; at < n && e == hipSuccess; at += h.chunk) {
         a.n = n - at < h.chunk ? n - at : h.chunk;
         a.X = X + at * a.d;
@@ -275,8 +275,9 @@ som_status run_eval_half(som_map *m, som::EvalArgs a, const som::HalfPlan &h, in
         a.idx2 = idx2 ? idx2 + at : nullptr;
         a.d1 = d1 ? d1 + at : nullptr;
         e = som::launch_split_rows(a.X, a.n, a.d, a.d, som::kHalfSamples, m->xhalf, m->xscale,
-                                   nullptr, m->stream);
+                                   bad + 1, false, m->stream);
         if (e == hipSuccess) e = som::launch_bmu_half(a, m->stream);
+        if (e == hipSuccess) e = som::launch_bmu_unsplit(a, m->num_cus, m->stream);
         if (e == hipSuccess) e = som::launch_bmu_rerank(a, m->stream);
     }
     return from_hip(e);

@@ -68,8 +68,8 @@ struct EvalSmem {
 
 // acc[i][j] = x.w over columns [k_begin, k_end) for the 16 x 16 MFMA tile
 // (i, j) of this wave: units u0 + wunit*64 + i*16 + 4*(lane/16) + v (v the
-// f4 component) and samples s0 + wsamp*32 + j*16 + lane%16.  k_begin is a
-// multiple of kBK; columns past d are zero.
+// f4 component) and samples s0 + wsamp*32 + j*16 + lane%16.  k_begin, and k_end
+// below d, are multiples of four; columns from k_end on are zero.
 // With kFull false (a unit tile that reaches past N) a wave multiplies only
 // its 16-unit MFMA tiles that hold units below u_end.
 template <bool kFull>
@@ -123,6 +123,7 @@ __device__ inline void tile_products(const EvalArgs &a, int64_t s0, int u0, int 
                                                   (col < a.ld ? col : a.ld - 4));
         }
     };
+    const int64_t w_end = k_end < a.d ? k_end : a.ld;  // (W's rows are zero past d)
     const auto stage = [&](int k0) {
 #pragma unroll
         for (int i = 0; i < kXPer; ++i) {
@@ -132,7 +133,7 @@ __device__ inline void tile_products(const EvalArgs &a, int64_t s0, int u0, int 
             f4 v = xv[i];
             const bool row_ok = s0 + r < a.n;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = (row_ok && col + e < a.d) ? v[e] : 0.f;
+            for (int e = 0; e < 4; ++e) v[e] = (row_ok && col + e < k_end) ? v[e] : 0.f;
             *reinterpret_cast<f4 *>(&sm.xs[r * kLdsStride + 4 * c4]) = v;
         }
 #pragma unroll
@@ -142,7 +143,7 @@ __device__ inline void tile_products(const EvalArgs &a, int64_t s0, int u0, int 
             const int64_t col = k0 + 4 * c4;
             const f4 zero = {0.f, 0.f, 0.f, 0.f};
             *reinterpret_cast<f4 *>(&sm.ws[r * kLdsStride + 4 * c4]) =
-                (u0 + r < u_end && col < a.ld) ? wv[i] : zero;
+                (u0 + r < u_end && col < w_end) ? wv[i] : zero;
         }
     };
     fetch(k_begin);
@@ -241,13 +242,9 @@ __device__ inline void empty_lists(float (&ts)[2][kCand], int (&tu)[2][kCand]) {
         for (int c = 0; c < kCand; ++c) { ts[j][c] = INFINITY; tu[j][c] = -1; }
 }
 
-// Fused form: sample tile blockIdx.x, unit group blockIdx.y (group_units
-// units, walked tile by tile over all of d).  Two workgroups per compute
-// unit (the register budget that allows, and the planner, assume it).
-__global__ __launch_bounds__(kEvalBlock, 2) void bmu_candidates_kernel(EvalArgs a) {
-    __shared__ __align__(16) EvalSmem sm;
-    const int64_t s0 = (int64_t)blockIdx.x * kBM;
-    const int grp = blockIdx.y;
+// Fused form: the samples from s0 on, unit group grp (group_units units, walked
+// tile by tile over all of d).
+__device__ inline void group_candidates(const EvalArgs &a, int64_t s0, int grp, EvalSmem &sm) {
     const int u_begin = grp * a.group_units;
     const int u_end = u_begin + a.group_units < a.N ? u_begin + a.group_units : a.N;
     float ts[2][kCand];
@@ -267,17 +264,22 @@ __global__ __launch_bounds__(kEvalBlock, 2) void bmu_candidates_kernel(EvalArgs 
     write_candidates(a, s0, grp, ts, tu, sm);
 }
 
-// Split form: the products of sample tile blockIdx.x with unit tile
-// blockIdx.y over columns [z * split_len, (z + 1) * split_len) of d,
-// z = blockIdx.z, stored sample-major: part[(z n + i) Np + u] for sample i
-// and unit u, Np = tiles_u * kBN (each lane's four consecutive units in one
-// 16-byte store).  The re-rank sums a sample's ranges in order.
-__global__ __launch_bounds__(kEvalBlock, 2) void bmu_partial_kernel(EvalArgs a) {
+// Two workgroups per compute unit (the register budget that allows, and the
+// planner, assume it).
+__global__ __launch_bounds__(kEvalBlock, 2) void bmu_candidates_kernel(EvalArgs a) {
     __shared__ __align__(16) EvalSmem sm;
-    const int64_t s0 = (int64_t)blockIdx.x * kBM;
-    const int u0 = blockIdx.y * kBN;
+    group_candidates(a, (int64_t)blockIdx.x * kBM, blockIdx.y, sm);
+}
+
+// Split form: the products of the samples from s0 on with unit tile utile over
+// columns [z * split_len, (z + 1) * split_len) of d, stored sample-major:
+// part[(z n + i) Np + u] for sample i and unit u, Np = tiles_u * kBN (each
+// lane's four consecutive units in one 16-byte store).  The re-rank sums a
+// sample's ranges in order.
+__device__ inline void range_products(const EvalArgs &a, int64_t s0, int utile, int z,
+                                      EvalSmem &sm) {
+    const int u0 = utile * kBN;
     const int u_end = u0 + kBN < a.N ? u0 + kBN : a.N;
-    const int z = blockIdx.z;
     const int k_begin = z * a.split_len;
     const int k_end = k_begin + a.split_len < a.d ? k_begin + a.split_len : a.d;
     f4 acc[4][2];
@@ -296,6 +298,33 @@ __global__ __launch_bounds__(kEvalBlock, 2) void bmu_partial_kernel(EvalArgs a) 
                                          u0 + wunit * 64 + (lane >> 4) * 4);
 #pragma unroll
         for (int i = 0; i < 4; ++i) row[i * 4] = acc[i][j];
+    }
+}
+
+__global__ __launch_bounds__(kEvalBlock, 2) void bmu_partial_kernel(EvalArgs a) {
+    __shared__ __align__(16) EvalSmem sm;
+    range_products(a, (int64_t)blockIdx.x * kBM, blockIdx.y, blockIdx.z, sm);
+}
+
+// Behind the products in halves (som_eval_half.hip), into their arrays: the fp32
+// products of every tile of kBM samples one of which has no halves, or of all
+// where a prototype has none (a NaN, an infinity, extreme values).  A search
+// without such rows pays one launch that leaves at once.
+__global__ __launch_bounds__(kEvalBlock, 2) void bmu_unsplit_kernel(EvalArgs a, int per_tile) {
+    __shared__ __align__(16) EvalSmem sm;
+    const bool all = a.bad[0] != 0;
+    if (!all && a.bad[1] == 0) return;
+    const int64_t tasks = (a.n + kBM - 1) / kBM * per_tile;
+    for (int64_t t = blockIdx.x; t < tasks; t += gridDim.x) {
+        const int64_t s0 = t / per_tile * kBM;
+        const int k = (int)(t % per_tile);
+        const int64_t smp = s0 + (threadIdx.x & (kBM - 1));
+        if (!all && __ballot(a.xscale[smp < a.n ? smp : a.n - 1] < 0.f) == 0) continue;
+        if (a.splits > 1)
+            range_products(a, s0, k % a.tiles_u, k / a.tiles_u, sm);
+        else
+            group_candidates(a, s0, k, sm);
+        __syncthreads();
     }
 }
 
@@ -330,19 +359,7 @@ __global__ __launch_bounds__(64 * kRerankWaves) void bmu_rerank_kernel(EvalArgs 
     int lu[kCand];
 #pragma unroll
     for (int c = 0; c < kCand; ++c) { ls[c] = INFINITY; lu[c] = -1; }
-    if (a.xhalf && (a.xscale[i] < 0.f || *a.w_bad != 0)) {
-        // the sample, or a prototype, could not be split into halves: every
-        // score in fp32 (such rows hold infinities, NaN or extreme values)
-        const float *x = a.X + i * a.d;
-        for (int u = 0; u < a.N; ++u) {
-            const float *w = a.W + (int64_t)u * a.ld;
-            float s = 0.f;
-            for (int64_t j = lane; j < a.d; j += 64) s = fmaf(x[j], w[j], s);
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-            if (lane == 0) insert_top(ls, lu, a.wnorm[u] - 2.f * s, u);
-        }
-    } else if (a.splits > 1) {
+    if (a.splits > 1) {
         // each lane's best units among 4 q .. 4 q + 3, q = lane, lane + 64, ...
         const int64_t np = (int64_t)a.tiles_u * kBN;
         const int nq = (a.N + 3) / 4;
@@ -692,6 +709,14 @@ hipError_t launch_bmu_candidates(const EvalArgs &a, hipStream_t s) {
         return hipErrorInvalidValue;
     bmu_partial_kernel<<<dim3((unsigned)a.tiles_s, (unsigned)a.tiles_u, (unsigned)a.splits),
                          dim3(kEvalBlock), 0, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_bmu_unsplit(const EvalArgs &a, int num_cus, hipStream_t s) {
+    if (!a.bad || !a.xscale || a.split_len % 4 != 0 || a.tiles_u != ceil_div(a.N, kBN))
+        return hipErrorInvalidValue;
+    const int per_tile = a.splits > 1 ? a.tiles_u * a.splits : a.ugroups;
+    bmu_unsplit_kernel<<<dim3((unsigned)(2 * num_cus)), dim3(kEvalBlock), 0, s>>>(a, per_tile);
     return hipGetLastError();
 }
 

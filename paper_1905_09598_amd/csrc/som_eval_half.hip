@@ -40,17 +40,18 @@ constexpr int kSlabHalves = (kHM + kHN) / 16 * kBlockHalves;
 constexpr float kRowLo = 0x1p-40f, kRowHi = 0x1p40f;       // row maxima that are split
 
 // 16 rows per workgroup: each row's scale, then its halves.  A row that holds
-// a NaN or an infinity or a magnitude above 2^40, and a sample (any_bad null)
-// whose largest one is below 2^-40, is stored as zeros with scale -1: the
-// re-rank searches it in fp32.  A prototype that small keeps the scale of 2^-40:
-// its halves are then exact to 2^-79, far below a rounding of the distance to a
-// sample that is not as small.
+// a NaN or an infinity or a magnitude above 2^40, and a sample (not small_ok)
+// whose largest one is below 2^-40, is stored as zeros with scale -1 and raises
+// *bad: its products are formed in fp32 (bmu_unsplit_kernel).  A prototype that
+// small keeps the scale of 2^-40: its halves are then exact to 2^-79, far below a
+// rounding of the distance to a sample that is not as small.
 // scale[row] = 2^-k; rows past `rows` are zero.  Bound by memory: the rows are
 // read twice, the second time from L2, and written once.
 template <bool VEC4>
 __global__ __launch_bounds__(256) void split_rows_kernel(const float *X, int64_t rows, int64_t ld,
                                                          int32_t d, int32_t slabs, _Float16 *out,
-                                                         float *scale, int32_t *any_bad) {
+                                                         float *scale, int32_t *bad,
+                                                         bool small_ok) {
     __shared__ float mul[16];
     const int t = threadIdx.x, r = t >> 4, c0 = t & 15;
     const int64_t row0 = (int64_t)blockIdx.x * 16;
@@ -80,13 +81,13 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float *X, int64_t
         for (int o = 8; o >= 1; o >>= 1) top = max(top, (unsigned)__shfl_xor((int)top, o, 64));
         if (c0 == 0) {
             const float big = __uint_as_float(top);
-            const bool fine = big <= kRowHi && (big >= kRowLo || top == 0 || any_bad);
+            const bool fine = big <= kRowHi && (big >= kRowLo || top == 0 || small_ok);
             // 2^14 <= big 2^k < 2^15
             const int k = top == 0 ? 0 : 14 - (max((int)(top >> 23), 127 - 40) - 127);
             mul[r] = fine ? ldexpf(1.f, k) : 0.f;
             if (row0 + r < rows) {
                 scale[row0 + r] = fine ? ldexpf(1.f, -k) : -1.f;
-                if (!fine && any_bad) atomicOr(any_bad, 1);
+                if (!fine) atomicOr(bad, 1);
             }
         }
     }
@@ -188,10 +189,20 @@ __device__ inline void half_products(const EvalArgs &a, int64_t stile, int64_t u
     __syncthreads();  // the buffers are free again
 }
 
+// Whether a workgroup's products are all formed in fp32 instead: a prototype
+// has no halves, or none of the tile's samples has.
+__device__ inline bool all_unsplit(const EvalArgs &a, int64_t s0) {
+    if (a.bad[0] != 0) return true;
+    if (a.bad[1] == 0) return false;
+    const int64_t smp = s0 + threadIdx.x;
+    return !__syncthreads_or((int)threadIdx.x < kHM && smp < a.n && a.xscale[smp] >= 0.f);
+}
+
 // Fused form: sample tile blockIdx.x, unit group blockIdx.y walked tile by
 // tile; per sample the kCand best (score, unit) pairs of the group.
 __global__ __launch_bounds__(kHThreads, 2) void half_candidates_kernel(EvalArgs a) {
     extern __shared__ __align__(16) _Float16 lds[];
+    if (all_unsplit(a, (int64_t)blockIdx.x * kHM)) return;
     const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int wsamp = wave & 3, wunit = wave >> 2;
@@ -251,6 +262,7 @@ __global__ __launch_bounds__(kHThreads, 2) void half_candidates_kernel(EvalArgs 
 // sample-major as the fp32 kernel writes them.
 __global__ __launch_bounds__(kHThreads, 2) void half_partial_kernel(EvalArgs a) {
     extern __shared__ __align__(16) _Float16 lds[];
+    if (all_unsplit(a, (int64_t)blockIdx.x * kHM)) return;
     const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int wsamp = wave & 3, wunit = wave >> 2;
@@ -356,19 +368,20 @@ bool plan_bmu_half(EvalArgs *a, int num_cus, uint64_t max_bytes, double fp32_us,
 }
 
 hipError_t launch_split_rows(const float *X, int64_t rows, int64_t ld, int32_t d, int tile,
-                             void *out, float *scale, int32_t *any_bad, hipStream_t s) {
+                             void *out, float *scale, int32_t *bad, bool small_ok,
+                             hipStream_t s) {
     const int32_t slabs = (int32_t)ceil_div(d, kHK);
     const dim3 grid((unsigned)(ceil_div(rows, tile) * (tile / 16)));
     const bool vec4 = d % 4 == 0 && ld % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
     (vec4 ? split_rows_kernel<true> : split_rows_kernel<false>)
         <<<grid, dim3(256), 0, s>>>(X, rows, ld, d, slabs, static_cast<_Float16 *>(out), scale,
-                                    any_bad);
+                                    bad, small_ok);
     return hipGetLastError();
 }
 
 hipError_t launch_bmu_half(const EvalArgs &a, hipStream_t s) {
     if (a.tiles_s != ceil_div(a.n, kHM) || a.tiles_u != ceil_div(a.N, kHN) || !a.xhalf ||
-        !a.whalf || a.slabs != ceil_div(a.d, kHK))
+        !a.whalf || !a.bad || a.slabs != ceil_div(a.d, kHK))
         return hipErrorInvalidValue;
     if (a.splits <= 1) {
         if (a.ugroups < 1 || a.group_units % kHN != 0 ||

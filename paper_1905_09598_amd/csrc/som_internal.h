@@ -158,7 +158,7 @@ hipError_t launch_prepare_train(const TrainArgs &a, float2 *sched, hipStream_t s
 // or infinity among the `count` floats at x.
 hipError_t launch_scan_finite(const float *x, int64_t count, DevState *state,
                               hipStream_t s);
-// out[u] = |W[u]|^2 for the N rows of W; *clear (nullable) = 0.
+// out[u] = |W[u]|^2 for the N rows of W; clear[0], clear[1] = 0 (nullable).
 hipError_t launch_row_sqnorm(const float *W, int64_t ld, int32_t N, float *out, int32_t *clear,
                              hipStream_t s);
 // Copy the n x d rows of X into out, rows of xld floats (xld >= d, a
@@ -188,7 +188,7 @@ struct EvalArgs {
     // otherwise
     const _Float16 *xhalf, *whalf;  // the rows' halves
     const float *xscale, *wscale;   // their scales (a sample's is -1 where it has none)
-    const int32_t *w_bad;           // nonzero: some prototype has none
+    const int32_t *bad;             // [0] nonzero: some prototype has none; [1]: some sample
     int32_t slabs;                  // slabs of 32 columns
 };
 constexpr int kCand = 4;
@@ -204,11 +204,14 @@ struct HalfPlan {
 bool plan_bmu_half(EvalArgs *a, int num_cus, uint64_t max_bytes, double fp32_us, HalfPlan *plan);
 // Halves that `rows` rows take, stored in whole tiles of `tile` rows.
 int64_t half_rows_halves(int64_t rows, int32_t d, int tile);
-// Split the rows of X (row pitch ld) into out, their scales into scale;
-// any_bad (nullable) is raised by a row that cannot be split.
+// Split the rows of X (row pitch ld) into out, their scales into scale; *bad is
+// raised by a row that cannot be split (with small_ok, rows of tiny values can).
 hipError_t launch_split_rows(const float *X, int64_t rows, int64_t ld, int32_t d, int tile,
-                             void *out, float *scale, int32_t *any_bad, hipStream_t s);
+                             void *out, float *scale, int32_t *bad, bool small_ok,
+                             hipStream_t s);
 hipError_t launch_bmu_half(const EvalArgs &a, hipStream_t s);
+// After launch_bmu_half: the fp32 products in its place where a.bad says so.
+hipError_t launch_bmu_unsplit(const EvalArgs &a, int num_cus, hipStream_t s);
 
 // The candidate search's shape for n samples over N units on `num_cus`
 // compute units (sets ugroups, group_units, splits, split_len, tiles_s,

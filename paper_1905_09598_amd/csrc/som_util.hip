@@ -122,7 +122,7 @@ __global__ void scan_finite_kernel(const float *x, int64_t count, DevState *stat
 __global__ __launch_bounds__(256) void row_sqnorm_kernel(const float *W, int64_t ld, int32_t N,
                                                          float *out, int tpr, int32_t *clear) {
     __shared__ double part[4];
-    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
+    if (clear && blockIdx.x == 0 && threadIdx.x < 2) clear[threadIdx.x] = 0;
     const int rsub = threadIdx.x / tpr, t = threadIdx.x - rsub * tpr;
     const int64_t row = (int64_t)blockIdx.x * (256 / tpr) + rsub;
     double acc = 0.0;
