@@ -100,10 +100,10 @@ int64_t pipe_block_dots_floats(int m, int64_t nsteps);
 hipError_t launch_train_pipe(const TrainArgs &a, const TrainPlan &plan, hipStream_t s);
 
 // Panel training (som_train_panel.hip): the same steps with the pass over the
-// prototypes as two matrix products per panel of m - 1 steps.
+// prototypes as two matrix products per panel of m steps.
 struct PanelPlan {
     int32_t instance = -1;    // kernel instance
-    int32_t m = 0;            // columns of a panel: its m - 1 steps and the next centre
+    int32_t m = 0;            // steps per panel
     int32_t controllers = 0;  // workgroups that run a panel's steps
     int32_t ctl_rows = 0;     // units of a controller whose coefficients LDS holds
     int32_t lds = 0;          // bytes of LDS of the control launch
@@ -117,11 +117,12 @@ struct PanelPlan {
 // Buffers are indexed by panel modulo their number.
 struct PanelArgs {
     TrainArgs t;
-    float *ec[2];     // (m + 1) x dpad: the columns less the centre, and the centre
-    float *xt[4];     // dpad x m: the columns' samples, transposed
+    float *ec[2];     // (m + 1) x dpad: column set less the centre, and the centre
+    float *xt[4];     // dpad x m: the steps' samples, transposed
     float *near[4];   // gsplit x 32: squared distances between the centre's candidates
-    float *gm[3];     // gsplit x m x m: products of the columns
-    float *gx[3];     // the same with the panel before's samples
+    int32_t *centre;  // 4: the centre's step within its panel
+    float *gm[3];     // gsplit x (m x m + 16): column set by own steps
+    float *gx[3];     // the same by the panel before's steps
     float *prod[2];   // ksplit x npad x m: the sweep's products
     double *qf[2];    // ksplit x npad: its squared norms
     float *gam[2];    // (m / 16) x npad x 16: coefficients of the panel's steps

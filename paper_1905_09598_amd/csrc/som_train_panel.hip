@@ -1,8 +1,8 @@
-// Panel training: the online steps of Eq. (1) in panels of M - 1 steps, with
-// the pass over the prototypes as two matrix products per panel and the steps
+// Panel training: the online steps of Eq. (1) in panels of M steps, with the
+// pass over the prototypes as two matrix products per panel and the steps
 // themselves in the space of inner products.
 //
-// Within panel b (steps s0 .. s0 + M - 2, samples x_k, z one of them) every
+// Within panel b (steps s0 .. s0 + M - 1, samples x_k, z one of them) every
 // prototype is w = z + v, and a step with factor h moves v to
 // (1 - h) v + h e_k, e_k = x_k - z.  With L_l = v . e_l and Q = |v|^2
 //     D_k = |x_k - w|^2 = G_kk - 2 L_k + Q,        G_kl = e_k . e_l,
@@ -25,10 +25,10 @@
 // are corrected once panel b's coefficients are known (correct): with a_j =
 // x_j - z' the panel's samples in the next panel's centring,
 //     (F_(b+1) - z') . e'_l = beta (F_b - z') . e'_l + sum_j gamma_j a_j . e'_l.
-// Q is carried from panel to panel through the column of the next centre, the
-// last of a panel's M, Q' = Q - 2 v . (z' - z) + |z' - z|^2, and pulled to the
-// sweep's |F_b - z'|^2 with weight beta^2, so its rounding does not add up over
-// panels.
+// Q is carried from panel to panel through the column of the next centre (in
+// the place of the panel's own centre, whose column would be zero),
+// Q' = Q - 2 v . (z' - z) + |z' - z|^2, and pulled to the sweep's |F_b - z'|^2
+// with weight beta^2, so its rounding does not add up over panels.
 //
 // Distances are differences of terms at the scale of |x_k - z|^2 and |w - z|^2,
 // so the centre has to lie among the samples: a panel's is, of eight of its
@@ -64,16 +64,11 @@ constexpr int kCandidates = 8;   // samples of a panel its centre is chosen from
 constexpr int kPairs = kCandidates * (kCandidates - 1) / 2;
 constexpr int kPairStride = 32;
 
-// Steps of a panel of M columns: the last column is the next centre's.
-template <int M>
-constexpr int panel_steps() {
-    return M - 1;
-}
 // Steps of panel `panel`.
 template <int M>
 __device__ inline int steps_of(const PanelArgs &p, int64_t panel) {
-    const int64_t left = p.t.nsteps - panel * panel_steps<M>();
-    return (int)(left < panel_steps<M>() ? left : panel_steps<M>());
+    const int64_t left = p.t.nsteps - panel * M;
+    return (int)(left < M ? left : M);
 }
 
 __device__ inline f4 mfma4(const f4 &a, const f4 &b, f4 c) {
@@ -318,21 +313,22 @@ __device__ inline const float *step_row(const PanelArgs &p, int64_t s) {
     return a.X + (int64_t)(idx >= 0 && idx < a.n ? idx : 0) * a.d;
 }
 
-// Sample row of a panel's candidate c for its centre.
+// Step, within its panel, of a panel's candidate c for its centre.
 template <int M>
-__device__ inline const float *candidate_row(const PanelArgs &p, int64_t panel, int c) {
-    return step_row(p, panel * panel_steps<M>() + steps_of<M>(p, panel) * c / kCandidates);
+__device__ inline int candidate_step(const PanelArgs &p, int64_t panel, int c) {
+    return steps_of<M>(p, panel) * c / kCandidates;
 }
 __device__ inline int pair_index(int i, int j) {  // i < j
     return i * (2 * kCandidates - 1 - i) / 2 + j - i - 1;
 }
 
-// Centre of a panel: of its candidates the one whose median squared distance to
-// the other seven is smallest (the lowest such).  Every wave finds it for
-// itself, lane l for candidate l % 8.
+// Centre of a panel, as its step within the panel: of its candidates the one
+// whose median squared distance to the other seven is smallest (the lowest
+// such; 0 for a panel past the call's last).  Every wave finds it for itself,
+// lane l for candidate l % 8.
 template <int M>
-__device__ inline const float *centre_row(const PanelArgs &p, int64_t panel) {
-    if (panel * panel_steps<M>() >= p.t.nsteps) return step_row(p, p.t.nsteps - 1);
+__device__ inline int centre_step(const PanelArgs &p, int64_t panel) {
+    if (panel * M >= p.t.nsteps) return 0;
     const int c = threadIdx.x & (kCandidates - 1);
     const float *near = p.near[panel & 3];
     float v[kCandidates - 1];
@@ -356,15 +352,20 @@ __device__ inline const float *centre_row(const PanelArgs &p, int64_t panel) {
         ((unsigned long long)__float_as_uint(median) << 32) | (unsigned)c;
 #pragma unroll
     for (int o = 1; o < kCandidates; o *= 2) key = u64_min(key, __shfl_xor(key, o, 64));
-    return candidate_row<M>(p, panel, __builtin_amdgcn_readfirstlane((int)(unsigned)key));
+    return candidate_step<M>(p, panel, __builtin_amdgcn_readfirstlane((int)(unsigned)key));
 }
 
-// Sample row of a panel's column l: its steps' samples, then the next panel's
-// centre.
+// Step whose sample is column l of a panel with centre step z: its steps, but
+// the next panel's centre (step `next` there) in the place of its own.
 template <int M>
-__device__ inline const float *column_row(const PanelArgs &p, int64_t panel, int l,
-                                          const float *next_centre) {
-    return l < panel_steps<M>() ? step_row(p, panel * panel_steps<M>() + l) : next_centre;
+__device__ inline int64_t column_step(int64_t panel, int l, int z, int next) {
+    return panel * M + (l == z ? M + next : l);
+}
+
+// Floats of one column range's part of a Gram matrix.
+template <int M>
+constexpr int gram_stride() {
+    return M * M + 16;
 }
 
 // Columns c .. c + 3 of a sample row, zero past d.
@@ -382,27 +383,26 @@ __device__ inline f4 row_f4(const PanelArgs &p, const float *x, int c) {
     return v;
 }
 
-// Gather task: columns 64 task .. of a panel: its columns less the centre into
-// ec (row M: the centre), and raw and transposed into xt (the last one, which is
-// no step, meets a coefficient of zero there).
+// Gather task: columns 64 task .. of a panel: its column set less the centre
+// into ec (row M: the centre), its steps' samples transposed into xt.
 template <int M>
 __device__ inline void gather_task(const PanelArgs &p, int64_t panel, int task, float *lds) {
     constexpr int P = kGatherDims + 1;
     const int t = threadIdx.x, c4 = t & 15, r0 = t >> 4;
     const int c = task * kGatherDims + 4 * c4;
     float *xt = p.xt[panel & 3], *ec = p.ec[panel & 1];
-    const float *next = centre_row<M>(p, panel + 1);
-    const f4 z = row_f4(p, centre_row<M>(p, panel), c);
+    const int zs = centre_step<M>(p, panel), next = centre_step<M>(p, panel + 1);
+    const f4 z = row_f4(p, step_row(p, panel * M + zs), c);
     f4 x[M / 16];
 #pragma unroll
     for (int k = 0; k < M / 16; ++k)
-        x[k] = row_f4(p, column_row<M>(p, panel, r0 + 16 * k, next), c);
+        x[k] = row_f4(p, step_row(p, column_step<M>(panel, r0 + 16 * k, zs, next)), c);
 #pragma unroll
     for (int k = 0; k < M / 16; ++k) {
         const int r = r0 + 16 * k;
         *reinterpret_cast<f4 *>(ec + (int64_t)r * p.dpad + c) = x[k] - z;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) lds[r * P + 4 * c4 + e] = x[k][e];
+        for (int e = 0; e < 4; ++e) lds[r * P + 4 * c4 + e] = r == zs ? z[e] : x[k][e];
     }
     if (r0 == 0) *reinterpret_cast<f4 *>(ec + (int64_t)M * p.dpad + c) = z;
     __syncthreads();
@@ -416,10 +416,10 @@ __device__ inline void gather_task(const PanelArgs &p, int64_t panel, int task, 
     }
 }
 
-// Gram task: one 16 x 16 tile of products of a panel's columns over column
-// range `part` of p.gsplit.  pair < M/16 (M/16 + 1) / 2: with each other, into
-// gm (both tiles of the pair); after that: with panel - 1's samples in this
-// panel's centring, into gx, [column l][step j].
+// Gram task: one 16 x 16 tile of products of a panel's column set over column
+// range `part` of p.gsplit.  pair < M/16 (M/16 + 1) / 2: with its own steps
+// e_j, into gm (both tiles of the pair); after that: with panel - 1's samples
+// in this panel's centring, into gx.  Both are [column l][step j].
 template <int M>
 __device__ inline void gram_task(const PanelArgs &p, int64_t panel, int pair, int part, f4 *lds) {
     constexpr int NT = M / 16, kOwn = NT * (NT + 1) / 2;
@@ -438,13 +438,13 @@ __device__ inline void gram_task(const PanelArgs &p, int64_t panel, int pair, in
         tj = (pair - kOwn) % NT;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, g = lane >> 4;
-    // (a wave-uniform branch around the centre's lane exchange)
-    const float *next = ti == NT - 1 || tj == NT - 1 ? centre_row<M>(p, panel + 1) : nullptr;
-    const float *xz = centre_row<M>(p, panel);
-    const float *xb = column_row<M>(p, panel, 16 * tj + i, next);
-    // (panel - 1 has no step M - 1: this panel's first, at a coefficient of zero)
-    const float *xa = own ? column_row<M>(p, panel, 16 * ti + i, next)
-                          : step_row(p, (panel - 1) * panel_steps<M>() + 16 * ti + i);
+    const int64_t s0 = panel * M;
+    const int z = centre_step<M>(p, panel), next = centre_step<M>(p, panel + 1);
+    if (pair == 0 && part == 0 && threadIdx.x == 0) p.centre[panel & 3] = z;
+    const float *xa = step_row(
+        p, own ? column_step<M>(panel, 16 * ti + i, z, next) : s0 - M + 16 * ti + i);
+    const float *xb = step_row(p, column_step<M>(panel, 16 * tj + i, z, next));
+    const float *xz = step_row(p, s0 + z);
     const int tiles = p.dpad / 16;
     const int k0 = (int)((int64_t)tiles * part / p.gsplit);
     const int k1 = (int)((int64_t)tiles * (part + 1) / p.gsplit);
@@ -468,10 +468,20 @@ __device__ inline void gram_task(const PanelArgs &p, int64_t panel, int pair, in
     if (wave > 0) return;
     acc = acc + lds[lane] + lds[64 + lane] + lds[128 + lane];
     // acc[v]: step 16 ti + 4 g + v, column 16 tj + i
-    float *G = (own ? p.gm : p.gx)[panel % 3] + (int64_t)part * (M * M);
+    float *G = (own ? p.gm : p.gx)[panel % 3] + (int64_t)part * gram_stride<M>();
+    // the centre's own step moves no column (its place among the columns holds
+    // the next centre, whose norm goes behind the matrix)
     if (own && ti != tj)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) G[(16 * ti + 4 * g + v) * M + 16 * tj + i] = acc[v];
+        for (int v = 0; v < 4; ++v)
+            G[(16 * ti + 4 * g + v) * M + 16 * tj + i] = 16 * tj + i == z ? 0.f : acc[v];
+    if (own)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (16 * ti + 4 * g + v == z) {
+                if (16 * tj + i == z) G[M * M] = acc[v];
+                acc[v] = 0.f;
+            }
     *reinterpret_cast<f4 *>(G + (16 * tj + i) * M + 16 * ti + 4 * g) = acc;
 }
 
@@ -495,13 +505,14 @@ __device__ inline void prepare_task(const PanelArgs &p, int64_t panel, int task,
 constexpr size_t kPrepareLds = 80 * (kGatherDims + 1) * 4;
 
 // Select task: the candidates' squared distances over column range `part`, from
-// direct differences, for centre_row.
+// direct differences, for centre_step.
 template <int M>
 __device__ inline void select_task(const PanelArgs &p, int64_t panel, int part, float *lds) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float *x[kCandidates];
 #pragma unroll
-    for (int c = 0; c < kCandidates; ++c) x[c] = candidate_row<M>(p, panel, c);
+    for (int c = 0; c < kCandidates; ++c)
+        x[c] = step_row(p, panel * M + candidate_step<M>(p, panel, c));
     const int quads = p.dpad / 4;
     const int q0 = (int)((int64_t)quads * part / p.gsplit);
     const int q1 = (int)((int64_t)quads * (part + 1) / p.gsplit);
@@ -572,7 +583,7 @@ __device__ inline void correct_tile(const PanelArgs &p, int64_t panel, int u0) {
                 f4 ga[NT];
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
-                    ga[t] = *reinterpret_cast<const f4 *>(gx + (int64_t)k * (M * M) +
+                    ga[t] = *reinterpret_cast<const f4 *>(gx + (int64_t)k * gram_stride<M>() +
                                                           (16 * t + i) * M + 16 * s + 4 * g);
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
@@ -669,7 +680,8 @@ template <int M, int U, int NW>
 struct ControlLds {
     static constexpr int kUnits = U * NW * 64;
     static constexpr int kGram = 0;
-    static constexpr int kKeys = M * M * 4;                       // [2][4 NW]
+    static constexpr int kCentre = M * M * 4;                     // M + 16 floats
+    static constexpr int kKeys = kCentre + (M + 16) * 4;          // [2][4 NW]
     static constexpr int kWhere = kKeys + 2 * 4 * NW * 8;         // [2][4 NW]
     static constexpr int kBlocks = kWhere + 2 * 4 * NW * 8;       // [M / 16][16][16] fp64
     static constexpr int kTrans = kBlocks + M * kSub * 8;         // 32 units a wave
@@ -700,14 +712,17 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
     const int base = GRID ? (int)blockIdx.x * Lds::kUnits : 0;
     const int mine = (wave * 64 + lane) * U;  // the lane's first unit of the workgroup's
     float *G = reinterpret_cast<float *>(lds + Lds::kGram);
+    float *centre = reinterpret_cast<float *>(lds + Lds::kCentre);
     float *T = reinterpret_cast<float *>(lds + Lds::kTrans) + wave * 32 * kTPitch;
     double *blocks = reinterpret_cast<double *>(lds + Lds::kBlocks);
     unsigned long long *keys = reinterpret_cast<unsigned long long *>(lds + Lds::kKeys);
     unsigned long long *where = reinterpret_cast<unsigned long long *>(lds + Lds::kWhere);
     float *cg = reinterpret_cast<float *>(lds + Lds::kCoef);   // [q][rows][16]
     float *cb = cg + (M / 16 - 1) * rows * kSub;               // [q][rows]
-    constexpr int kNext = panel_steps<M>();  // (and the next centre's column)
-    const int64_t s0 = panel * kNext;
+    const int64_t s0 = panel * M;
+    // the centre's step; its column is the next centre's
+    const int z = __builtin_amdgcn_readfirstlane(__hip_atomic_load(
+        p.centre + (panel & 3), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     const int nst = steps_of<M>(p, panel);
     const bool bad = a.state->order_bad != 0;  // used where the BMUs are traced
 
@@ -721,7 +736,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
                      p.pc + (int64_t)min(base + mine + u, a.N - 1) * M + kSub * sub);
     };
     fetch(0);
-    double Q[U], lz[U], bsub[U];  // bsub: product of the panel's beta so far
+    double Q[U], Lz[U], bsub[U];  // bsub: product of the panel's beta so far
     float row[U], col[U];
     const float rscale = a.topology == 1 ? 0.75f : 1.f;
     const float shift = a.topology == 1 ? 0.5f : 0.f;
@@ -732,7 +747,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
         const int at = min(unit, a.N - 1);
         const double q = p.qc[at];
         Q[u] = unit < a.N ? q : (double)INFINITY;  // a unit past N is never nearest
-        lz[u] = p.pc[(int64_t)at * M + kNext];
+        Lz[u] = p.pc[(int64_t)at * M + z];
         bsub[u] = 1.0;
         int r, c;
         unit_rc(at, a.cols, inv_cols, r, c);
@@ -741,7 +756,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
         col[u] = (float)c + shift * (float)(r & 1);
     }
     {
-        // the Gram matrix
+        // the Gram matrix; the next centre's row apart, zero in its place
         const float *src = p.gm[panel % 3];
         constexpr int kTotal = M * M / 4, kStep = NW * 64, kBatch = 5;
         for (int e0 = threadIdx.x; e0 < kTotal; e0 += kBatch * kStep) {
@@ -753,20 +768,28 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
 #pragma unroll
                 for (int n = 0; n < kBatch; ++n)
                     v[n] = v[n] + reinterpret_cast<const f4 *>(
-                                      src + (int64_t)k * (M * M))[min(e0 + n * kStep,
+                                      src + (int64_t)k * gram_stride<M>())[min(e0 + n * kStep,
                                                                                kTotal - 1)];
 #pragma unroll
             for (int n = 0; n < kBatch; ++n) {
                 const int e = e0 + n * kStep;
+                const f4 zero = {0.f, 0.f, 0.f, 0.f};
                 if (e < kTotal) {
-                    reinterpret_cast<f4 *>(G)[e] = v[n];
                     const int l = 4 * e / M, c = 4 * e % M;
+                    if (l == z) reinterpret_cast<f4 *>(centre)[c / 4] = v[n];
+                    const f4 r = l == z ? zero : v[n];
+                    reinterpret_cast<f4 *>(G)[e] = r;
                     if (l / kSub == c / kSub)
 #pragma unroll
                         for (int x = 0; x < 4; ++x)
-                            blocks[l * kSub + c % kSub + x] = (double)v[n][x];
+                            blocks[l * kSub + c % kSub + x] = (double)r[x];
                 }
             }
+        }
+        if (threadIdx.x == 0) {
+            float zz = src[M * M];
+            for (int k = 1; k < p.gsplit; ++k) zz += src[(int64_t)k * gram_stride<M>() + M * M];
+            centre[M] = zz;
         }
         if (NW > 1 && threadIdx.x < 2 * 4 * NW) keys[threadIdx.x] = 0ull;
     }
@@ -774,10 +797,10 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
         __syncthreads();
     else
         __builtin_amdgcn_wave_barrier();
-    const double zz = (double)G[kNext * M + kNext];  // |z' - z|^2
+    const double zz = (double)centre[M];  // |z' - z|^2
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        if (base + mine + u < a.N) p.qe[base + mine + u] = fma(-2.0, lz[u], Q[u]) + zz;
+        if (base + mine + u < a.N) p.qe[base + mine + u] = fma(-2.0, Lz[u], Q[u]) + zz;
     PollRegs<4> polls;
 #pragma unroll
     for (int q = 0; q < 4; ++q) polls.v[q] = 0;
@@ -796,7 +819,8 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int k = 0; k < kSub; ++k) L[u][k] = bsub[u] * ahead[u][k];
+            for (int k = 0; k < kSub; ++k)
+                L[u][k] = kSub * sub + k == z ? 0.0 : bsub[u] * ahead[u][k];
         fetch(sub + 1 < M / 16 ? sub + 1 : sub);
         if (sub > 0) {
             // the panel's earlier coefficients, from zero in fp32
@@ -856,11 +880,13 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
 #pragma unroll
             for (int k = 0; k < kSub; ++k) hs[u][k] = 0.f;
         const double *Gs = blocks + sub * kSub * kSub;
-        // lane k holds the k-th step's schedule entry and the Gram entries
-        // (k, k) and (k, k + 1), which the chain of a step needs at once
+        // lane k holds the k-th step's schedule entry, the Gram entries (k, k)
+        // and (k, k + 1), which the chain of a step needs at once, and the
+        // step's product with the next centre
         const int lk = lane & (kSub - 1);
         const float2 sched = fetch_entry(a, s0 + kSub * sub + lk, float2());
         const double diag = Gs[lk * (kSub + 1)];
+        const float zcol = centre[kSub * sub + lk];
         const double above = Gs[lk * (kSub + 1) + (lk + 1 < kSub)];
         int trace = 0;
         double grow[kSub];  // the last step's row of the Gram matrix
@@ -886,6 +912,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
             const int64_t s = s0 + kSub * sub + k;
             const float lr = lane_f(sched.x, k), c2 = lane_f(sched.y, k);
             const double gkk = lane_d(diag, k), gk1 = lane_d(above, k);
+            const double gkz = (double)lane_f(zcol, k);
             // The distances as integers: positive ones in order, negative ones
             // (the rounding of a distance near zero) below them, a NaN as inf.
             double D[U];
@@ -976,13 +1003,12 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
                 Q[u] = fma(hd, fma(hd, D[u], -D[u]) + (gkk - Q[u]), Q[u]);
                 if constexpr (k + 1 < kSub)
                     L[u][k + 1] = fma(hd, gk1 - L[u][k + 1], L[u][k + 1]);
+                Lz[u] = fma(hd, gkz - Lz[u], Lz[u]);
                 hp[u] = hd;
             }
             return true;
         });
         if (GRID && !ok) return false;
-#pragma unroll
-        for (int u = 0; u < U; ++u) lz[u] = L[u][kSub - 1];  // at last the next centre's
         if (blockIdx.x == 0 && wave == 0 && a.bmu_trace && !bad && lane < kSub &&
             kSub * sub + lane < nst)
             a.bmu_trace[s0 + kSub * sub + lane] = trace;
@@ -1021,7 +1047,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        if (base + mine + u < a.N) p.qn[base + mine + u] = fma(-2.0, lz[u], Q[u]) + zz;
+        if (base + mine + u < a.N) p.qn[base + mine + u] = fma(-2.0, Lz[u], Q[u]) + zz;
     return true;
 }
 
@@ -1190,7 +1216,7 @@ __global__ __launch_bounds__(256, 2) void panel_grid_kernel(PanelArgs p) {
     const uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
     const int C = p.controllers, b = blockIdx.x, others = (int)gridDim.x - C;
     if (b < C && b >= C - p.absent) return;
-    const int64_t panels = (a.nsteps + panel_steps<M>() - 1) / panel_steps<M>();
+    const int64_t panels = (a.nsteps + M - 1) / M;
     const int nsweep = (a.N + 16 * TU - 1) / (16 * TU) * p.ksplit;
     unsigned n = 0;
     for (int t = b; t < (panels < 4 ? (int)panels : 4) * p.gsplit; t += gridDim.x) {
@@ -1361,7 +1387,7 @@ int64_t panel_floats(const PanelPlan &pl, PanelArgs *p, float *base) {
         *at = p ? reinterpret_cast<std::remove_reference_t<decltype(**at)> *>(base + off) : nullptr;
         off += (count * (int64_t)(sizeof(**at) / sizeof(float)) + 63) & ~(int64_t)63;
     };
-    const int64_t gram = (int64_t)pl.gsplit * pl.m * pl.m;
+    const int64_t gram = (int64_t)pl.gsplit * (pl.m * pl.m + 16);
     for (int k = 0; k < 2; ++k) {
         take(&a.ec[k], (int64_t)(pl.m + 1) * pl.dpad);
         take(&a.prod[k], (int64_t)pl.ksplit * pl.npad * pl.m);
@@ -1381,6 +1407,7 @@ int64_t panel_floats(const PanelPlan &pl, PanelArgs *p, float *base) {
     take(&a.qc, (int64_t)pl.npad);
     take(&a.qn, (int64_t)pl.npad);
     take(&a.qe, (int64_t)pl.npad);
+    take(&a.centre, (int64_t)64);
     take(&a.arrived, (int64_t)64);
     return off;
 }
@@ -1407,7 +1434,7 @@ hipError_t launch_train_panel(const PanelArgs &args, const PanelPlan &pl, hipStr
         return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(in.whole), dim3(pl.grid),
                                           dim3(256), params, (unsigned)pl.lds, s);
     }
-    const int64_t panels = (p.t.nsteps + pl.m - 2) / (pl.m - 1);
+    const int64_t panels = (p.t.nsteps + pl.m - 1) / pl.m;
     const int nsweep = (p.t.N + 16 * in.tu - 1) / (16 * in.tu) * pl.ksplit;
     const dim3 block(64 * in.nw);
     const size_t side_lds = in.lds(0);

@@ -148,7 +148,7 @@ def test_outliers_do_not_cost_the_other_steps_their_bmus(rows, cols, M, factor):
     d, n = 64, 4 * M + 30
     rng = np.random.default_rng(M)
     X = rng.standard_normal((n, d)).astype(np.float32)
-    for at in (2 * M, 3 * (M - 1), M + 7):
+    for at in (2 * M, 3 * M, M + 7):
         X[at] *= np.float32(factor)
     W0 = rng.standard_normal((rows * cols, d)).astype(np.float32)
     order = np.arange(n, dtype=np.int32)
