@@ -232,13 +232,15 @@ som_status som_train_batch(som_map *map, const float *X, int64_t n, int32_t epoc
  * over ranges of d, and the ranges summed in order, when there are too few
  * samples to fill the chip otherwise); the four best by that score are
  * re-ranked by direct fp32 distances.  The products are fp32, or for large
- * calls fp16 instructions on operands held in two fp16 halves, whose error
- * against fp64 is no larger; rows that halves cannot hold (a NaN, an
- * infinity, magnitudes above 2^40, samples below 2^-40) are ranked in fp32.
- * Scratch (candidate lists of 32 bytes per sample and unit group, or 512
- * bytes per sample, range and 128 units of partial products when d is split;
- * for the halves 4 bytes per prototype element and per element of up to
- * 256 MiB of samples at a time) is kept by the map.
+ * calls on rows of 32 floats and more fp16 instructions on operands held in
+ * two fp16 halves, whose error against fp64 is no larger; rows that halves
+ * cannot hold (a NaN, an infinity, magnitudes above 2^40, samples below
+ * 2^-40) are ranked in fp32.  Up to 8 samples take the direct fp32 distances
+ * of all units instead.  Scratch (candidate lists of 32 bytes per sample and
+ * unit group, or 512 bytes per sample, range and 128 units of partial
+ * products when d is split; for the halves 4 bytes per prototype element and
+ * per element of up to 256 MiB of samples at a time; 4 N bytes per sample of
+ * the direct search) is kept by the map.
  * out_idx is a device int32 array of n entries.  Stream-ordered. */
 som_status som_bmu(som_map *map, const float *X, int64_t n, int32_t *out_idx);
 

@@ -1,11 +1,12 @@
 // The batched BMU's products X W^T for large calls, on the fp16 matrix
 // instructions (v_mfma_f32_16x16x32_f16, fp32 accumulation) at fp32 precision:
-// every operand is split into two halves, x 2^k = hi + lo + e with |e| <= 2^-23
-// |x 2^k| (hi the nearest fp16, lo the fp16 nearest to the rest, k a power of
-// two per row that puts its largest magnitude just below 2^15), and a product
-// is hi hi' + hi lo' + lo hi'.  What is left out, lo lo' and e, is at most
-// 2^-21.4 of a term at random signs, below the rounding of an fp32 sum over d
-// terms.  Three instructions of 16 cycles replace eight of 32.
+// every operand is split into two halves, x 2^k = hi + lo + e with |e| <=
+// max(2^-23 |x 2^k|, 2^-25) (hi the nearest fp16, lo the fp16 nearest to the
+// rest, k a power of two per row that puts its largest magnitude just below
+// 2^15), and a product is hi hi' + hi lo' + lo hi'.  What is left out, lo lo' and
+// e, is at most 2^-21.4 of a term at random signs, below the rounding of an fp32
+// sum of 32 terms and more (kMinCols).  Three instructions of 16 cycles replace
+// eight of 32.
 //
 // Measured at 100,000 samples x 10,000 units x 2048: the whole evaluation 12.3
 // ms, 332 TFLOP/s of fp32 products, against 40.2 ms and 102 TFLOP/s on the fp32
@@ -308,6 +309,14 @@ constexpr size_t kHalfLds = 2 * (size_t)kSlabHalves * sizeof(_Float16);
 // on 20 x 20 units the fp32 kernel (46 us) stays.
 constexpr double kSlabUs = 1.2, kTileUs = 3.0, kLaunchUs = 3.0;
 constexpr int64_t kChunkBytes = 256 << 20;  // samples split at a time
+// A sum of fewer terms has fewer roundings than the halves leave out.  Root mean
+// square error of a score over |x| |w| against fp64 (emulated, norms summed in
+// fp64 on both sides), fp32 products and halves: Gaussian rows of 2, 4, 8, 16, 24
+// and 32 columns 9.2e-8 and 1.5e-7, 7.0e-8 and 1.0e-7, 6.0e-8 and 7.7e-8, 5.7e-8
+// and 6.2e-8, 5.4e-8 and 5.3e-8, 5.4e-8 and 5.1e-8; clusters of 16, 24, 32 and 64
+// columns 6.3e-8 and 6.8e-8, 7.4e-8 and 6.2e-8, 7.8e-8 and 6.0e-8, 9.3e-8 and
+// 5.6e-8.
+constexpr int kMinCols = 32;
 
 }  // namespace
 

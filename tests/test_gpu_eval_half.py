@@ -96,6 +96,27 @@ def test_rows_that_cannot_be_split_match_the_fp32_products(where):
     m.close()
 
 
+# Rows of fewer than 32 floats keep to the fp32 products, whose few roundings
+# come to less than what halves leave out.
+@pytest.mark.parametrize("d", [2, 3, 8, 31, 32])
+def test_short_rows_keep_the_fp32_products(d):
+    torch = torch_cuda()
+    rows, cols, n = 32, 32, 40000
+    X, W = _case(rows, cols, d, n, d)
+    m = som.Map(rows, cols, d, seed=0)
+    m.weights = dev(W)
+    assert m.bmu_route(n) == ("fp32" if d < 32 else "halves")
+    Xd = dev(X)
+    a = m.bmu(Xd, second=True)
+    b = [torch.empty(n, dtype=t, device="cuda") for t in (torch.int32, torch.int32, torch.float32)]
+    som.som_bmu2_noalloc(m.handle, Xd, n, *b)
+    m.synchronize()
+    if d < 32:
+        assert all(torch.equal(p, q) for p, q in zip(a, b))
+    assert (a[0] == b[0]).float().mean() > 0.999
+    m.close()
+
+
 # Rows without halves send their tiles to the fp32 products, not every sample to a
 # scan of all prototypes: the search takes no longer than a small multiple of the
 # search that forms every product in fp32 (it was 10 times that and more).
