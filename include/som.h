@@ -325,7 +325,8 @@ som_status som_shuffle(uint64_t seed, int64_t epoch, int64_t n, int32_t *out);
  * host array lambda[2], and optionally the column means (mean) and the
  * unit eigenvectors (v1, v2; sign such that the component of largest
  * magnitude, lowest index on ties, is positive) into device arrays of d
- * floats.  Computed on the device (fp32 matrix-core covariance, fp64-reduced
+ * floats.  Where the data leave a direction open (rank 1, a single sample) any
+ * unit vector at a right angle to v1 stands for it; with d = 1, v2 is zero.  Computed on the device (fp32 matrix-core covariance, fp64-reduced
  * subspace iteration until both residuals are below 2e-5 lambda[0], at most
  * 4000 iterations) with d * d + 144 d floats of work memory allocated for
  * the call; ordered on `stream` (a hipStream_t, NULL for the null stream),

@@ -468,33 +468,88 @@ __global__ void start_basis_kernel(float *V, int64_t count, uint64_t seed) {
     V[i] = (float)((double)(z >> 40) * (1.0 / 16777216.0) - 0.5);
 }
 
-// Sign convention: the component of largest magnitude (lowest index on
-// ties) of each of the two vectors is made positive.
-__global__ __launch_bounds__(kOrthThreads) void sign_fix_kernel(float *V, int32_t d) {
+// Sum over the workgroup's threads, in a fixed order, to every thread.
+__device__ inline double block_sum(double v, double (&red)[kOrthThreads / 64]) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double s = red[0];
+    for (int w = 1; w < kOrthThreads / 64; ++w) s += red[w];
+    return s;
+}
+
+// Smallest key of the workgroup's threads, to every thread.
+__device__ inline unsigned long long block_min(unsigned long long k,
+                                               unsigned long long (&best)[kOrthThreads / 64]) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const unsigned long long other = __shfl_xor(k, o, 64);
+        k = other < k ? other : k;
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) best[threadIdx.x >> 6] = k;
+    __syncthreads();
+    unsigned long long m = best[0];
+    for (int w = 1; w < kOrthThreads / 64; ++w) m = best[w] < m ? best[w] : m;
+    return m;
+}
+
+// One workgroup: the two Ritz vectors as unit vectors at a right angle (any such
+// pair has the eigenvalue 0 where the data have no variance).  A direction that
+// vanished in the iteration (data of rank 1, a single sample) is zero until here:
+// v1 becomes the first axis, v2 the axis on which v1 is smallest less its part
+// along v1.  Vectors within 1e-3 of that already stay as they are.  Then the sign
+// convention: the component of largest magnitude (lowest index on ties) of each
+// is made positive.
+__global__ __launch_bounds__(kOrthThreads) void finish_vectors_kernel(float *V, int32_t d) {
     __shared__ unsigned long long best[kOrthThreads / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ double red[kOrthThreads / 64];
+    const int tid = threadIdx.x;
+    float *v1 = V;
+    for (int a = 0; a < 2 && a < d; ++a) {
+        float *v = V + (int64_t)a * d;
+        double sq = 0.0, dot = 0.0;
+        for (int64_t j = tid; j < d; j += kOrthThreads) {
+            sq = fma((double)v[j], (double)v[j], sq);
+            if (a > 0) dot = fma((double)v[j], (double)v1[j], dot);
+        }
+        sq = block_sum(sq, red);
+        dot = block_sum(dot, red);
+        if (!(sq == sq) || (fabs(sq - 1.0) <= 1e-3 && fabs(dot) <= 1e-3)) continue;
+        const double left = sq - dot * dot;
+        if (left > 1e-6) {
+            const double inv = 1.0 / sqrt(left);
+            for (int64_t j = tid; j < d; j += kOrthThreads)
+                v[j] = (float)(((double)v[j] - (a > 0 ? dot * (double)v1[j] : 0.0)) * inv);
+        } else {
+            unsigned long long k = ~0ull;  // (|v1| bits, index)
+            for (int64_t j = tid; j < d; j += kOrthThreads) {
+                const unsigned mag = a > 0 ? __float_as_uint(fabsf(v1[j])) : 0u;
+                const unsigned long long key = ((unsigned long long)mag << 32) | (unsigned)j;
+                k = key < k ? key : k;
+            }
+            const int64_t axis = (int64_t)(unsigned)block_min(k, best);
+            const double on = a > 0 ? (double)v1[axis] : 0.0, inv = 1.0 / sqrt(1.0 - on * on);
+            for (int64_t j = tid; j < d; j += kOrthThreads)
+                v[j] = (float)(((j == axis ? 1.0 : 0.0) - (a > 0 ? on * (double)v1[j] : 0.0)) * inv);
+        }
+        __syncthreads();
+    }
     for (int a = 0; a < 2; ++a) {
+        float *v = V + (int64_t)a * d;
         unsigned long long k = ~0ull;  // (~|v| bits, index): the minimum is the largest |v|
         for (int64_t j = tid; j < d; j += kOrthThreads) {
-            const unsigned mag = __float_as_uint(fabsf(V[(int64_t)a * d + j]));
+            const unsigned mag = __float_as_uint(fabsf(v[j]));
             const unsigned long long key = ((unsigned long long)(~mag) << 32) | (unsigned)j;
             k = key < k ? key : k;
         }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            const unsigned long long other = __shfl_xor(k, o, 64);
-            k = other < k ? other : k;
-        }
-        __syncthreads();
-        if (lane == 0) best[wave] = k;
-        __syncthreads();
-        unsigned long long m = best[0];
-        for (int w = 1; w < kOrthThreads / 64; ++w) m = best[w] < m ? best[w] : m;
-        const int j = (int)(unsigned)(m & 0xffffffffull);
-        const bool flip = V[(int64_t)a * d + j] < 0.f;
+        const int64_t j = (int64_t)(unsigned)block_min(k, best);
+        const bool flip = v[j] < 0.f;
         __syncthreads();
         if (flip)
-            for (int64_t i = tid; i < d; i += kOrthThreads) V[(int64_t)a * d + i] = -V[(int64_t)a * d + i];
+            for (int64_t i = tid; i < d; i += kOrthThreads) v[i] = -v[i];
         __syncthreads();
     }
 }
@@ -578,7 +633,7 @@ hipError_t pca_top2(const float *X, int64_t n, int32_t d, float *work, float *me
         if ((h[2] <= tol * scale && h[3] <= tol * scale) || it >= max_iters) break;
     }
     // final Rayleigh-Ritz pair of the next basis in `vectors` (columns 0, 1),
-    // signs fixed
+    // unit vectors with their signs fixed
     matvec_kernel<<<dim3(mv_blocks), dim3(256), 0, s>>>(C, d, in, R, out, part);
     orthonormal_kernel<<<dim3(1), dim3(kSmallThreads), 0, s>>>(part, (int)mv_blocks, Q, stats, 1,
                                                               1);
@@ -588,7 +643,7 @@ hipError_t pca_top2(const float *X, int64_t n, int32_t d, float *work, float *me
                            s);
         if (e != hipSuccess) return e;
     }
-    sign_fix_kernel<<<dim3(1), dim3(kOrthThreads), 0, s>>>(vectors, d);
+    finish_vectors_kernel<<<dim3(1), dim3(kOrthThreads), 0, s>>>(vectors, d);
     e = hipMemcpyAsync(h, stats, sizeof(h), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;

@@ -95,6 +95,24 @@ def test_components_at_tile_edges(n, d):
                 assert np.abs(V[:, a] - V_o[:, a]).max() <= 2e-5 / gap + 1e-5
 
 
+@pytest.mark.parametrize("n,d", [(50, 2), (50, 7), (64, 40), (300, 2049)])
+@pytest.mark.parametrize("rank", [0, 1])
+def test_vectors_are_unit_where_the_data_have_no_second_direction(n, d, rank):
+    rng = np.random.default_rng(n + d)
+    X = np.ones((n, d), np.float32)
+    axis = rng.standard_normal(d)
+    if rank:
+        X = (X + np.outer(rng.standard_normal(n), axis)).astype(np.float32)
+    lam, mean, V = _gpu_pca(X)
+    say(f"rank {rank} n={n} d={d}: {lam}", V.T @ V)
+    # unit and at a right angle within fp32 rounding of d components
+    assert np.abs(V.T @ V - np.eye(2)).max() <= 1e-5
+    assert lam[1] <= 2e-5 * max(lam[0], 1e-30)
+    if rank:
+        # the sums' rounding turns the axis by less than 2e-5 of the eigenvalue
+        assert abs(V[:, 0] @ axis) / np.linalg.norm(axis) >= 1 - 1e-4
+
+
 def test_linear_init_matches_oracle_grid():
     rng = np.random.default_rng(9)
     d = 40
