@@ -45,7 +45,10 @@
  *     training kernels (default 20 s); SOM_DEBUG_ABSENT_WORKGROUP=1 makes
  *     som_train launch one workgroup fewer than its exchanges wait for, so
  *     every wait runs into that bound, every workgroup leaves its loop, and
- *     the next synchronizing call reports SOM_E_TIMEOUT.
+ *     the next synchronizing call reports SOM_E_TIMEOUT;
+ *     SOM_DEBUG_NO_ROUTE_MEMORY=1 makes panel training and the search in
+ *     halves find no memory for their buffers, as on a full device: the call
+ *     takes the persistent kernel or the fp32 products instead.
  *   - Device pointer extents are checked against the allocation that holds
  *     the pointer (hipMemGetAddressRange).  Under a pooling allocator (for
  *     example torch's caching allocator) that allocation can be a larger
@@ -359,9 +362,9 @@ som_status som_suggest_size(int64_t m, double lambda1, double lambda2, int32_t *
 som_status som_init_linear(som_map *map, const float *X, int64_t n);
 
 /* How som_train would run a call of nsteps steps on this map, and som_bmu,
- * som_bmu2, som_evaluate and the batch map a search of n samples (an
- * allocation that fails then can still lead to the persistent kernel or to the
- * fp32 products). */
+ * som_bmu2, som_evaluate and the batch map a search of n samples (where the
+ * device has no memory for the panels' or the halves' buffers the call still
+ * takes the persistent kernel or the fp32 products). */
 enum { SOM_TRAIN_PERSISTENT = 0, SOM_TRAIN_PANELS = 1 };
 enum { SOM_BMU_DIRECT = 0, SOM_BMU_FP32 = 1, SOM_BMU_HALVES = 2 };
 som_status som_train_route(const som_map *map, int64_t nsteps, int32_t *route);

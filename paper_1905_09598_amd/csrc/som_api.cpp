@@ -64,11 +64,10 @@ struct som_map {
     int64_t cand_cap = 0;
     float *part = nullptr;
     int64_t part_cap = 0;
-    // the search's rows in halves: samples (one chunk) and prototypes, with
-    // their scales; the flags of rows without halves follow the prototypes' scales
-    void *xhalf = nullptr, *whalf = nullptr;
-    float *xscale = nullptr, *wscale = nullptr;
-    int64_t xhalf_cap = 0, whalf_cap = 0, xscale_cap = 0, wscale_cap = 0;
+    // the search in halves (half_layout): prototypes, samples (one chunk), their
+    // scales, the flags of rows without halves, candidate lists or partial products
+    unsigned char *half = nullptr;
+    int64_t half_cap = 0;
     float *d1 = nullptr;
     double *sums = nullptr;
     int64_t eval_cap = 0;
@@ -178,6 +177,19 @@ hipError_t ensure(som_map *m, T **p, int64_t *cap, int64_t need) {
     return e;
 }
 
+// ensure() for memory that only a faster route needs: false, with no error left
+// behind, where the device has none to give, and the call takes the other route.
+// SOM_DEBUG_NO_ROUTE_MEMORY=1 (failure-path tests): as if it had none.
+template <typename T>
+bool ensure_route(som_map *m, T **p, int64_t *cap, int64_t need, hipError_t *error) {
+    const char *none = getenv("SOM_DEBUG_NO_ROUTE_MEMORY");
+    const hipError_t e = none && none[0] == '1' && none[1] == '\0' ? hipErrorOutOfMemory
+                                                                   : ensure(m, p, cap, need);
+    if (e == hipErrorOutOfMemory) (void)hipGetLastError();
+    *error = e == hipErrorOutOfMemory ? hipSuccess : e;
+    return e == hipSuccess;
+}
+
 // Evaluation scratch for n samples, ncand candidate-list entries (int32)
 // and npart partial products.  A capacity is zeroed before its buffers are
 // replaced and set again only once every one of them is allocated, so a
@@ -227,54 +239,72 @@ som_status check_deferred(som_map *m) {
     return e != hipSuccess ? from_hip(e) : take_status(m, st);
 }
 
+// Byte offsets of the buffer of a search in halves, chunks of `rows` samples: one
+// allocation on a map's first search instead of five (20 x 20 units of 2000
+// floats, 4000 samples: a map's first evaluation 217 us with five, 196 with one;
+// 172 on the fp32 products, which launch three kernels fewer).
+struct HalfLayout {
+    int64_t w, x, xscale, wscale, bad, lists, bytes;
+};
+HalfLayout half_layout(const som::EvalArgs &a, const som::HalfPlan &h, int64_t rows) {
+    HalfLayout l{};
+    const auto take = [&](int64_t bytes) {
+        const int64_t at = l.bytes;
+        l.bytes += (bytes + 255) / 256 * 256;
+        return at;
+    };
+    l.w = take(som::half_rows_halves(a.N, a.d, som::kHalfUnits) * (int64_t)sizeof(_Float16));
+    l.x = take(som::half_rows_halves(rows, a.d, som::kHalfSamples) * (int64_t)sizeof(_Float16));
+    l.xscale = take(rows * (int64_t)sizeof(float));
+    l.wscale = take((int64_t)a.N * (int64_t)sizeof(float));
+    l.bad = take(2 * sizeof(int32_t));
+    l.lists = take(som::half_lists_bytes(h, rows, a.N));
+    return l;
+}
+
 // The search with its products on the fp16 matrix instructions, one chunk of
 // samples after the other (the halves of a chunk stay in the Infinity Cache
-// between being written and read).
+// between being written and read).  *done false: the device has no memory for
+// the halves, and nothing was launched.
 som_status run_eval_half(som_map *m, som::EvalArgs a, const som::HalfPlan &h, int32_t *idx1,
-                         int32_t *idx2, float *d1) {
+                         int32_t *idx2, float *d1, bool *done) {
     const float *X = a.X;
     const int64_t n = a.n;
     const int64_t rows = n < h.chunk ? n : h.chunk;
+    const HalfLayout at = half_layout(a, h, rows);
+    hipError_t e;
+    *done = ensure_route(m, &m->half, &m->half_cap, at.bytes, &e);
+    if (!*done) return from_hip(e);
     a.splits = h.splits;
     a.split_len = h.split_len;
     a.ugroups = h.ugroups;
     a.group_units = h.group_units;
     a.slabs = h.slabs;
     a.tiles_u = (a.N + som::kHalfUnits - 1) / som::kHalfUnits;
-    const int64_t ncand = h.splits > 1 ? 0 : rows * (int64_t)h.ugroups * som::kCand * 2;
-    const int64_t npart =
-        h.splits > 1 ? (int64_t)h.splits * rows * a.tiles_u * som::kHalfUnits : 0;
-    som_status st = ensure_eval_scratch(m, rows, ncand, npart);
-    if (st != SOM_OK) return st;
-    const int64_t xh = som::half_rows_halves(rows, a.d, som::kHalfSamples);
-    const int64_t wh = som::half_rows_halves(a.N, a.d, som::kHalfUnits);
-    hipError_t e = ensure(m, reinterpret_cast<_Float16 **>(&m->xhalf), &m->xhalf_cap, xh);
-    if (e == hipSuccess) e = ensure(m, reinterpret_cast<_Float16 **>(&m->whalf), &m->whalf_cap, wh);
-    if (e == hipSuccess) e = ensure(m, &m->xscale, &m->xscale_cap, rows);
-    if (e == hipSuccess) e = ensure(m, &m->wscale, &m->wscale_cap, (int64_t)a.N + 2);
-    if (e != hipSuccess) return from_hip(e);
     a.wnorm = m->wnorm;
-    a.cand = m->cand;
-    a.part = m->part;
-    a.xhalf = static_cast<const _Float16 *>(m->xhalf);
-    a.whalf = static_cast<const _Float16 *>(m->whalf);
-    a.xscale = m->xscale;
-    a.wscale = m->wscale;
-    int32_t *bad = reinterpret_cast<int32_t *>(m->wscale + a.N);
+    a.cand = reinterpret_cast<int32_t *>(m->half + at.lists);
+    a.part = reinterpret_cast<float *>(m->half + at.lists);
+    float *xscale = reinterpret_cast<float *>(m->half + at.xscale);
+    float *wscale = reinterpret_cast<float *>(m->half + at.wscale);
+    int32_t *bad = reinterpret_cast<int32_t *>(m->half + at.bad);
+    a.xhalf = reinterpret_cast<const _Float16 *>(m->half + at.x);
+    a.whalf = reinterpret_cast<const _Float16 *>(m->half + at.w);
+    a.xscale = xscale;
+    a.wscale = wscale;
     a.bad = bad;
     a.x_vec4 = (m->d % 4 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0);
     e = som::launch_row_sqnorm(m->W, m->ld, m->N, m->wnorm, bad, m->stream);
     if (e == hipSuccess)
-        e = som::launch_split_rows(m->W, a.N, m->ld, a.d, som::kHalfUnits, m->whalf, m->wscale, bad,
-                                   true, m->stream);
-    for (int64_t at = 0; at < n && e == hipSuccess; at += h.chunk) {
-        a.n = n - at < h.chunk ? n - at : h.chunk;
-        a.X = X + at * a.d;
+        e = som::launch_split_rows(m->W, a.N, m->ld, a.d, som::kHalfUnits, m->half + at.w, wscale,
+                                   bad, true, m->stream);
+    for (int64_t i0 = 0; i0 < n && e == hipSuccess; i0 += h.chunk) {
+        a.n = n - i0 < h.chunk ? n - i0 : h.chunk;
+        a.X = X + i0 * a.d;
         a.tiles_s = (int32_t)((a.n + som::kHalfSamples - 1) / som::kHalfSamples);
-        a.idx1 = idx1 + at;
-        a.idx2 = idx2 ? idx2 + at : nullptr;
-        a.d1 = d1 ? d1 + at : nullptr;
-        e = som::launch_split_rows(a.X, a.n, a.d, a.d, som::kHalfSamples, m->xhalf, m->xscale,
+        a.idx1 = idx1 + i0;
+        a.idx2 = idx2 ? idx2 + i0 : nullptr;
+        a.d1 = d1 ? d1 + i0 : nullptr;
+        e = som::launch_split_rows(a.X, a.n, a.d, a.d, som::kHalfSamples, m->half + at.x, xscale,
                                    bad + 1, false, m->stream);
         if (e == hipSuccess) e = som::launch_bmu_half(a, m->stream);
         if (e == hipSuccess) e = som::launch_bmu_unsplit(a, m->num_cus, m->stream);
@@ -326,7 +356,11 @@ som_status run_eval(som_map *m, const float *X, int64_t n, int32_t *idx1,
         a.x_vec4 = (m->d % 4 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0);
         return from_hip(som::launch_bmu_few(a, m->part, m->stream));
     }
-    if (route == SOM_BMU_HALVES) return run_eval_half(m, a, half, idx1, idx2, d1);
+    if (route == SOM_BMU_HALVES) {
+        bool done = false;
+        const som_status half_st = run_eval_half(m, a, half, idx1, idx2, d1, &done);
+        if (half_st != SOM_OK || done) return half_st;
+    }
     som_status st = ensure_eval_scratch(m, n, som::bmu_cand_ints(a), som::bmu_part_floats(a));
     if (st != SOM_OK) return st;
     a.wnorm = m->wnorm;
@@ -446,10 +480,7 @@ som_status som_destroy(som_map *m) {
     (void)hipFree(m->wnorm);
     (void)hipFree(m->cand);
     (void)hipFree(m->part);
-    (void)hipFree(m->xhalf);
-    (void)hipFree(m->whalf);
-    (void)hipFree(m->xscale);
-    (void)hipFree(m->wscale);
+    (void)hipFree(m->half);
     (void)hipFree(m->idx1);
     (void)hipFree(m->idx2);
     (void)hipFree(m->d1);
@@ -772,7 +803,8 @@ static bool plan_panels(const som_map *m, const som::TrainArgs &a, const som::Tr
            (uint64_t)som::panel_floats(*plan, nullptr, nullptr) * sizeof(float) <= max_bytes();
 }
 
-// A training call in panels where plan_panels says so; *done tells.
+// A training call in panels where plan_panels says so and the device has memory for
+// their buffers; *done tells.
 static som_status train_panels(som_map *m, const som_schedule *s, som::TrainArgs &a,
                                const som::TrainPlan &persistent, int64_t nsteps, int64_t total,
                                bool *done) {
@@ -780,8 +812,9 @@ static som_status train_panels(som_map *m, const som_schedule *s, som::TrainArgs
     som::PanelPlan plan;
     if (!plan_panels(m, a, persistent, nsteps, &plan)) return SOM_OK;
     const int64_t floats = som::panel_floats(plan, nullptr, nullptr);
-    hipError_t e = stage_steps(m, s, a.n, nsteps, total, a);
-    if (e == hipSuccess) e = ensure(m, &m->panel, &m->panel_cap, floats);
+    hipError_t e;
+    if (!ensure_route(m, &m->panel, &m->panel_cap, floats, &e)) return from_hip(e);
+    e = stage_steps(m, s, a.n, nsteps, total, a);
     if (e != hipSuccess) return from_hip(e);
     a.grid = plan.controllers;
     a.slot_spread = 1;  // polls four deep: packed slots

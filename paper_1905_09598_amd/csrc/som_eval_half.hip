@@ -324,27 +324,37 @@ int64_t half_rows_halves(int64_t rows, int32_t d, int tile) {
     return ceil_div(rows, tile) * (tile / 16) * ceil_div(d, kHK) * kBlockHalves;
 }
 
+int64_t half_lists_bytes(const HalfPlan &plan, int64_t rows, int32_t N) {
+    return plan.splits > 1 ? plan.splits * rows * ceil_div(N, kHN) * kHN * (int64_t)sizeof(float)
+                           : rows * plan.ugroups * kCand * (int64_t)sizeof(int2);
+}
+
 bool plan_bmu_half(EvalArgs *a, int num_cus, uint64_t max_bytes, double fp32_us, HalfPlan *plan) {
     // Few tiles of 256 x 128 leave the chip idle while a workgroup walks a long
     // row: microseconds with the fp32 products and with halves, 9 samples of
     // 12000 on 25 units 50 and 159, 1500 of 2000 on 400 units 56 and 64; 1307 of
     // 186 on 5200 units 120 and 90.
     const bool asked = isinf(fp32_us);
-    if (!asked && a->n * (int64_t)a->N < (int64_t)1 << 20) return false;
+    if (!asked && (a->d < kMinCols || a->n * (int64_t)a->N < (int64_t)1 << 20)) return false;
     const int64_t slabs = ceil_div(a->d, kHK), tiles_u = ceil_div(a->N, kHN);
     const int64_t row_bytes = slabs * kHK * 4;
-    if ((uint64_t)half_rows_halves(a->N, a->d, kHN) * 2 > max_bytes) return false;
-    int64_t chunk = std::min<int64_t>(kChunkBytes, (int64_t)std::min<uint64_t>(max_bytes, INT64_MAX)) /
-                    (row_bytes * kHM) * kHM;
+    // one buffer holds the halves, the scales (4 bytes a row) and the lists
+    const uint64_t w_bytes = (uint64_t)half_rows_halves(a->N, a->d, kHN) * 2 + 4 * (uint64_t)a->N +
+                             2048;
+    if (w_bytes > max_bytes) return false;
+    const uint64_t left = std::min<uint64_t>(max_bytes - w_bytes, INT64_MAX);
+    int64_t chunk = std::min<int64_t>(kChunkBytes / row_bytes, (int64_t)left / (row_bytes + 4)) /
+                    kHM * kHM;
     if (chunk < kHM) return false;
     // equal chunks: a short last one would leave most of the chip idle
     const int64_t chunks = ceil_div(a->n, chunk);
     chunk = ceil_div(ceil_div(a->n, chunks), kHM) * kHM;
     const int64_t tiles_s = chunk / kHM;
+    const uint64_t lists_max = left - (uint64_t)chunk * (row_bytes + 4);
     double best = 1e300;
     for (int64_t tpg = tiles_u; tpg >= 1; --tpg) {
         const int64_t g = ceil_div(tiles_u, tpg);
-        if ((uint64_t)chunk * g * kCand * 8 > max_bytes) break;
+        if ((uint64_t)chunk * g * kCand * 8 > lists_max) break;
         const double us = ceil_div(tiles_s * g, num_cus) * (tpg * (slabs * kSlabUs + 1.0) + kTileUs) +
                           (double)chunk * g * kCand * 1e-5;
         if (us < best) {
@@ -358,7 +368,7 @@ bool plan_bmu_half(EvalArgs *a, int num_cus, uint64_t max_bytes, double fp32_us,
     for (int64_t S = 2; S <= 16 && S <= slabs; ++S) {
         const int64_t len = ceil_div(slabs, S), Se = ceil_div(slabs, len);
         const uint64_t part = (uint64_t)Se * chunk * tiles_u * kHN * 4;
-        if (Se != S || part > max_bytes) continue;
+        if (Se != S || part > lists_max) continue;
         const double us = ceil_div(tiles_s * tiles_u * Se, num_cus) * (len * kSlabUs + kTileUs) +
                           2.0 * (double)part / 5e6;
         if (us < best) {

@@ -203,6 +203,8 @@ struct HalfPlan {
 // True (and *plan set) when that is expected to take less than fp32_us (infinity:
 // wherever its scratch fits the cap).
 bool plan_bmu_half(EvalArgs *a, int num_cus, uint64_t max_bytes, double fp32_us, HalfPlan *plan);
+// Bytes of such a search's candidate lists, or partial products when it splits d.
+int64_t half_lists_bytes(const HalfPlan &plan, int64_t rows, int32_t N);
 // Halves that `rows` rows take, stored in whole tiles of `tile` rows.
 int64_t half_rows_halves(int64_t rows, int32_t d, int tile);
 // Split the rows of X (row pitch ld) into out, their scales into scale; *bad is

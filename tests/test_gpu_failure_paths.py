@@ -234,3 +234,50 @@ def test_exchange_timeout_ends_the_grid_and_is_reported(rows, cols, d, variant, 
     m.synchronize()
     assert np.array_equal(m.weights.cpu().numpy(), _fresh_training(rows, cols, d, W, X, order))
     m.close()
+
+
+# On a device without memory for the panels' or the halves' buffers the calls run
+# as they do without them, whatever the map trained or searched before.
+@pytest.mark.parametrize("rows,cols,d,n,before", [(10, 10, 500, 300, False), (40, 40, 5000, 300, True)])
+def test_training_without_memory_for_panels(rows, cols, d, n, before, monkeypatch):
+    X = dev(workloads.gaussian_mixture(n, d, 4, 0.2, seed=5))
+    W = workloads.random_weights(rows * cols, d, 6)
+    order = dev(workloads.epoch_orders(n, 1, 7))
+    m = _map(rows, cols, d, W)
+    assert m.train_route(n) == "panels"
+    if before:
+        m.train(X[:200], 1, *SCHED, order=dev(workloads.epoch_orders(200, 1, 7)))
+    out = []
+    for name, value in (("SOM_DEBUG_NO_ROUTE_MEMORY", "1"), ("SOM_MAX_BYTES", "100000")):
+        m.weights = dev(W)
+        monkeypatch.setenv(name, value)
+        m.train(X, 1, *SCHED, order=order)
+        m.synchronize()
+        monkeypatch.delenv(name)
+        out.append(m.weights.cpu().numpy())
+    assert np.array_equal(out[0], out[1])
+    m.weights = dev(W)
+    m.train(X, 1, *SCHED, order=order)           # panels again
+    m.synchronize()
+    assert bool(torch_cuda().isfinite(m.weights).all())
+    m.close()
+
+
+def test_search_without_memory_for_halves(monkeypatch):
+    torch = torch_cuda()
+    rows, cols, d, n = 32, 40, 128, 20000
+    W = workloads.random_weights(rows * cols, d, 2)
+    Xd = dev(workloads.gaussian_mixture(n, d, 4, 0.2, seed=3))
+    m = _map(rows, cols, d, W)
+    assert m.bmu_route(n) == "halves"
+    monkeypatch.setenv("SOM_DEBUG_NO_ROUTE_MEMORY", "1")
+    a = m.bmu(Xd, second=True)
+    qe = m.evaluate(Xd)[1]
+    monkeypatch.delenv("SOM_DEBUG_NO_ROUTE_MEMORY")
+    monkeypatch.setenv("SOM_BMU_ROUTE", "1")
+    b = m.bmu(Xd, second=True)
+    assert m.evaluate(Xd)[1] == qe
+    monkeypatch.delenv("SOM_BMU_ROUTE")
+    assert all(torch.equal(p, q) for p, q in zip(a, b))
+    assert (m.bmu(Xd) == a[0]).float().mean() > 0.999    # halves again
+    m.close()
