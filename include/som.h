@@ -42,10 +42,12 @@
  *     it returns SOM_E_OOM before allocating, and the map stays usable.
  *   - Failure-path switches (environment, for tests of the error paths only):
  *     SOM_DEBUG_EXCHANGE_TIMEOUT_US bounds each grid-exchange wait of the
- *     training kernels (default 20 s); SOM_DEBUG_ABSENT_WORKGROUP=1 makes
- *     som_train launch one workgroup fewer than its exchanges wait for, so
- *     every wait runs into that bound, every workgroup leaves its loop, and
- *     the next synchronizing call reports SOM_E_TIMEOUT;
+ *     training kernels and, in panels on one workgroup, the waits of a panel's
+ *     waves for each other (default 20 s, there counted in polls: 20 to 40 s);
+ *     SOM_DEBUG_ABSENT_WORKGROUP=1 makes som_train launch one workgroup fewer
+ *     than its exchanges wait for (there one wave fewer), so every wait runs
+ *     into that bound, every workgroup leaves its loop, and the next
+ *     synchronizing call reports SOM_E_TIMEOUT;
  *     SOM_DEBUG_NO_ROUTE_MEMORY=1 makes panel training and the search in
  *     halves find no memory for their buffers, as on a full device: the call
  *     takes the persistent kernel or the fp32 products instead.

@@ -774,7 +774,8 @@ static bool train_call_ok(const som_schedule *s, int64_t n, int32_t epochs, int6
 }
 
 // SOM_DEBUG_ABSENT_WORKGROUP=1 (failure-path tests): one workgroup fewer than
-// the exchanges wait for takes part, so that every exchange wait of the call
+// the exchanges wait for takes part (one wave fewer where a single workgroup's
+// waves wait for each other), so that every exchange wait of the call
 // runs into its time bound and the training ends with SOM_E_TIMEOUT.
 static bool absent_requested() {
     const char *ab = getenv("SOM_DEBUG_ABSENT_WORKGROUP");
@@ -825,7 +826,7 @@ static som_status train_panels(som_map *m, const som_schedule *s, som::TrainArgs
     p.t = a;
     (void)som::panel_floats(plan, &p, m->panel);
     p.x_vec4 = (m->d % 4 == 0) && (reinterpret_cast<uintptr_t>(a.X) % 16 == 0);
-    p.absent = plan.controllers > 1 && absent_requested() ? 1 : 0;
+    p.absent = m->N > plan.lane_units * 64 && absent_requested() ? 1 : 0;
     *done = true;
     return from_hip(som::launch_train_panel(p, plan, m->stream));
 }

@@ -104,6 +104,7 @@ hipError_t launch_train_pipe(const TrainArgs &a, const TrainPlan &plan, hipStrea
 struct PanelPlan {
     int32_t instance = -1;    // kernel instance
     int32_t m = 0;            // steps per panel
+    int32_t lane_units = 1;   // units a lane of a controller holds
     int32_t controllers = 0;  // workgroups that run a panel's steps
     int32_t ctl_rows = 0;     // units of a controller whose coefficients LDS holds
     int32_t lds = 0;          // bytes of LDS of the control launch
@@ -133,7 +134,8 @@ struct PanelArgs {
     int32_t dpad, npad, ksplit, gsplit, prep, controllers, ctl_rows;
     int32_t correct;  // products are corrected by a launch of their own
     int32_t x_vec4;   // sample rows are whole aligned float4s
-    int32_t absent;   // controllers that leave at once (failure-path tests)
+    int32_t absent;   // 1: a controller, or a wave of the only one, leaves at once (tests)
+    int32_t max_looks;  // failed looks at the other waves' keys that end a panel
 };
 // The panel shape for N units of d floats; false when the build has none.
 bool plan_train_panel(int32_t N, int32_t d, int num_cus, int max_lds, PanelPlan *plan);

@@ -691,11 +691,20 @@ struct ControlLds {
     }
 };
 
-// The steps of one panel for a workgroup's units; false once an exchange was
-// given up.  A lane holds, for each of its units, Q and the L columns of the
-// current 16 steps; at the start of each 16 they are formed from the panel's
-// starting products and its earlier coefficients (matrix instructions, then
-// through LDS from the accumulators' layout to one unit per lane).
+// A bounded wait ran into its bound: the call ends with SOM_E_TIMEOUT, and what
+// is still to run of it leaves.
+__device__ inline void give_up(const TrainArgs &a) {
+    __hip_atomic_store(&a.state->status, kStatusTimeout, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&a.state->order_bad, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The steps of one panel for a workgroup's units; false once an exchange, or a
+// wait for the workgroup's other waves, was given up.  A lane holds, for each of
+// its units, Q and the L columns of the current 16 steps; at the start of each 16
+// they are formed from the panel's starting products and its earlier coefficients
+// (matrix instructions, then through LDS from the accumulators' layout to one unit
+// per lane).
 //
 // What bounds it: on one workgroup the chain of a step, distance - row
 // minimum - LDS - minimum - factor, about 90 dependent instructions and one
@@ -811,7 +820,13 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
     // would keep the other waves from overwriting, two steps on, those it
     // still waits for.
     if (!GRID && wave * 64 >= lanes) return true;
+    // (failure-path tests: the last wave with units does not take part)
+    if (!GRID && p.absent && (wave + 1) * 64 >= lanes) return true;
     const int wave_rows = min((lanes - wave * 64 + 15) / 16, 4);  // rows with units
+    // Looks left at the keys this lane waits for in this panel: the bound of its
+    // waits.  Beyond it the steps run on with what they have, until the end of
+    // their 16.  (A counter of its own for every wait cost 1.2-2.5 % of a call.)
+    int looks = waits ? p.max_looks : 0;
 
     for (int sub = 0; sub * kSub < nst; ++sub) {
         // ---- L columns of the 16 steps
@@ -976,12 +991,13 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
                 later_columns(kk);
                 unsigned long long v, w;
                 do {
+                    --looks;
                     v = __hip_atomic_load(slots + (lane & (4 * NW - 1)), __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_WORKGROUP);
                     __atomic_signal_fence(__ATOMIC_SEQ_CST);
                     w = __hip_atomic_load(pos + (lane & (4 * NW - 1)), __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-                } while (__ballot(waits && ((unsigned)(v >> kUnitBits) & 0xffu) != tag) != 0);
+                } while (__ballot(looks >= 0 && ((unsigned)(v >> kUnitBits) & 0xffu) != tag) != 0);
                 const int hi = waits ? (int)(v >> 32) : 0x7fffffff;
                 int mh = row_min_i32(hi);
                 if constexpr (NW == 8) mh = rows01_min_i32(mh);
@@ -1009,6 +1025,10 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
             return true;
         });
         if (GRID && !ok) return false;
+        if (!GRID && __ballot(waits && looks < 0) != 0) {
+            give_up(a);
+            return false;
+        }
         if (blockIdx.x == 0 && wave == 0 && a.bmu_trace && !bad && lane < kSub &&
             kSub * sub + lane < nst)
             a.bmu_trace[s0 + kSub * sub + lane] = trace;
@@ -1101,6 +1121,7 @@ __global__ __launch_bounds__(64 * NW, 2) void panel_step_kernel(PanelArgs p, Sid
         side_task<M, TU, NW>(p, w, (int)blockIdx.x - 1, smem);
         return;
     }
+    if (p.t.state->order_bad) return;  // unusable input, or an earlier panel was given up
     if (!p.correct) {
         for (int t = threadIdx.x >> 6; t * 16 < p.t.N; t += NW) correct_tile<M>(p, panel, t * 16);
         __syncthreads();
@@ -1130,12 +1151,7 @@ __device__ inline bool grid_barrier(const PanelArgs &p, unsigned n, unsigned cha
             if (out) break;
             __builtin_amdgcn_s_sleep(1);
         }
-        if (out == 2) {
-            __hip_atomic_store(&a.state->status, kStatusTimeout, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&a.state->order_bad, 2, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (out == 2) give_up(a);
         __threadfence();
         *gone = out;
     }
@@ -1337,6 +1353,7 @@ bool plan_train_panel(int32_t N, int32_t d, int num_cus, int max_lds, PanelPlan 
         }
         plan->instance = k;
         plan->m = in.m;
+        plan->lane_units = in.u;
         plan->controllers = wgs;
         plan->ctl_rows = rows;
         plan->lds = (int32_t)lds;
@@ -1423,9 +1440,11 @@ hipError_t launch_train_panel(const PanelArgs &args, const PanelPlan &pl, hipStr
     p.controllers = pl.controllers;
     p.ctl_rows = pl.ctl_rows;
     p.t.grid = pl.controllers;
-    if (p.dpad > p.t.ld || p.absent < 0 || p.absent >= std::max(pl.controllers, 1) ||
-        p.t.nsteps < 1)
+    if (p.dpad > p.t.ld || p.absent < 0 || p.absent > 1 ||
+        (p.absent && pl.controllers < 2 && p.t.N <= 64 * in.u) || p.t.nsteps < 1)
         return hipErrorInvalidValue;
+    // a look takes 60-100 ns, 6-10 ticks
+    p.max_looks = (int32_t)std::min<uint64_t>(p.t.timeout_ticks / 6, INT32_MAX);
     hipError_t e;
     if (in.grid) {
         panel_zero_kernel<<<1, 1, 0, s>>>(p.arrived);

@@ -291,6 +291,35 @@ def test_exchange_timeout_ends_the_grid_and_is_reported(monkeypatch):
     m.close()
 
 
+# On one workgroup a wave waits for the others through LDS: those waits end too,
+# and the panels behind the one that was given up leave at once.
+@pytest.mark.parametrize("rows,cols", [(9, 11), (16, 17), (30, 31)])
+def test_wave_timeout_ends_the_call_and_is_reported(rows, cols, monkeypatch):
+    d, n = 64, 1000
+    X = dev(workloads.gaussian_mixture(n, d, 3, 0.2, seed=7))
+    W = workloads.random_weights(rows * cols, d, 8)
+    order = dev(workloads.epoch_orders(n, 1, 9))
+    m = som.Map(rows, cols, d, seed=0)
+    m.weights = dev(W)
+    monkeypatch.setenv("SOM_DEBUG_EXCHANGE_TIMEOUT_US", "5000")
+    monkeypatch.setenv("SOM_DEBUG_ABSENT_WORKGROUP", "1")
+    m.train(X, 1, 0.5, 0.05, 3.0, 0.5, order=order)
+    with pytest.raises(som.SomError) as e:
+        m.synchronize()
+    assert e.value.name == "SOM_E_TIMEOUT"
+    m.synchronize()
+    monkeypatch.delenv("SOM_DEBUG_ABSENT_WORKGROUP")
+    monkeypatch.delenv("SOM_DEBUG_EXCHANGE_TIMEOUT_US")
+    out = []
+    for _ in range(2):
+        m.weights = dev(W)
+        m.train(X, 1, 0.5, 0.05, 3.0, 0.5, order=order)
+        m.synchronize()
+        out.append(m.weights.cpu().numpy())
+    assert np.array_equal(out[0], out[1]) and np.isfinite(out[0]).all()
+    m.close()
+
+
 @pytest.mark.parametrize("rows,cols,d,n", [(10, 10, 500, 400), (30, 30, 300, 300),
                                            (60, 50, 300, 300)])
 def test_memory_cap_takes_the_grid_kernels(rows, cols, d, n, monkeypatch):
