@@ -299,8 +299,9 @@ __global__ __launch_bounds__(kHThreads, 2) void half_partial_kernel(EvalArgs a) 
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 constexpr size_t kHalfLds = 2 * (size_t)kSlabHalves * sizeof(_Float16);
-// Microseconds of one slab of a tile on a workgroup (1.2 on few tiles, up to 1.7
-// with every compute unit busy), of one workgroup's start and finish, and of the
+// Microseconds of one slab of a tile on a workgroup (1.2 on few tiles, where the
+// line lies; up to 1.7 with every compute unit busy, where the halves take a third
+// of the fp32 products' time), of one workgroup's start and finish, and of the
 // two extra launches; the rows are split at about 3 TB/s.  The line against the
 // fp32 kernels lies where these add up to less than those kernels' measured
 // 4.3 us per slice.  Evaluations on either side, fp32 and halves in
@@ -331,19 +332,27 @@ int64_t half_lists_bytes(const HalfPlan &plan, int64_t rows, int32_t N) {
 
 bool plan_bmu_half(EvalArgs *a, int num_cus, uint64_t max_bytes, double fp32_us, HalfPlan *plan) {
     // Few tiles of 256 x 128 leave the chip idle while a workgroup walks a long
-    // row: microseconds with the fp32 products and with halves, 9 samples of
-    // 12000 on 25 units 50 and 159, 1500 of 2000 on 400 units 56 and 64; 1307 of
-    // 186 on 5200 units 120 and 90.
+    // row, and the times above are those of a busier one; calls of fewer than 2^20
+    // sample-unit pairs stay on the fp32 products.  Microseconds of a search with
+    // the fp32 products and with halves, below that line: 9 samples of 12000 floats
+    // on 25 units 52 and 160, 1500 of 2000 on 400 58 and 69, 100 of 2048 on 10,000
+    // 131 and 151, 2600 of 2000 on 400 79 and 77, 400 of 10000 on 2500 292 and 241;
+    // above it, halves by the times above: 2700 of 2000 on 400 101 and 77, 200 and
+    // 255 of 2048 on 10,000 184 and 155, 187 and 157, 420 of 10000 on 2500 294 and
+    // 243, 2700 of 12000 on 400 366 and 326, 1307 of 186 on 5200 70 and 59; fp32 by
+    // them: 45,000 of 12000 on 25 1326 and 2833, 20,000 of 2000 on 100 156 and 205,
+    // 100 of 512 on 65,536 140 and 172.
     const bool asked = isinf(fp32_us);
     if (!asked && (a->d < kMinCols || a->n * (int64_t)a->N < (int64_t)1 << 20)) return false;
     const int64_t slabs = ceil_div(a->d, kHK), tiles_u = ceil_div(a->N, kHN);
     const int64_t row_bytes = slabs * kHK * 4;
-    // one buffer holds the halves, the scales (4 bytes a row) and the lists
+    // one buffer holds the halves, the scales (4 bytes a row) and the lists, at
+    // least those of one unit group
     const uint64_t w_bytes = (uint64_t)half_rows_halves(a->N, a->d, kHN) * 2 + 4 * (uint64_t)a->N +
                              2048;
     if (w_bytes > max_bytes) return false;
     const uint64_t left = std::min<uint64_t>(max_bytes - w_bytes, INT64_MAX);
-    int64_t chunk = std::min<int64_t>(kChunkBytes / row_bytes, (int64_t)left / (row_bytes + 4)) /
+    int64_t chunk = std::min<int64_t>(kChunkBytes / row_bytes, (int64_t)left / (row_bytes + 4 + kCand * 8)) /
                     kHM * kHM;
     if (chunk < kHM) return false;
     // equal chunks: a short last one would leave most of the chip idle

@@ -24,7 +24,8 @@ def _case(rows, cols, d, n, seed):
 
 
 # sample tiles of 256, unit tiles of 128, slabs of 32 columns; the larger
-# shapes take several chunks or unit groups, the longer rows split columns
+# shapes take several unit groups, the longer rows split columns (all in one chunk
+# of samples: test_chunks_of_samples has several)
 @pytest.mark.parametrize("rows,cols,d,n,offset", [
     (32, 40, 700, 12032, 0),      # whole tiles
     (31, 41, 701, 12033, 0),      # remainders everywhere, rows not whole float4s
@@ -93,6 +94,65 @@ def test_rows_that_cannot_be_split_match_the_fp32_products(where):
     both = np.isfinite(a[2]) & np.isfinite(b[2])
     assert np.array_equal(np.isfinite(a[2]), np.isfinite(b[2]))
     assert np.allclose(a[2][both], b[2][both], rtol=1e-5)
+    m.close()
+
+
+# Fewer samples than one tile on a large map, still in halves.
+@pytest.mark.parametrize("n", [106, 200, 255])
+def test_fewer_samples_than_a_tile(n, monkeypatch):
+    rows, cols, d = 100, 100, 1000
+    X = workloads.gaussian_mixture(n, d, 8, 0.2, 5)
+    W = workloads.random_weights(rows * cols, d, 6, -1.0, 1.0)
+    W[::50] = X[np.arange(200) % n] + 0.3 * W[::50]
+    monkeypatch.setenv("SOM_BMU_ROUTE", "2")
+    m = som.Map(rows, cols, d, seed=0)
+    m.weights = dev(W)
+    assert m.bmu_route(n) == "halves"
+    idx, idx2, d1 = [t.cpu().numpy() for t in m.bmu(dev(X), second=True)]
+    m.close()
+    o = oracle.evaluate(W, rows, cols, X)
+    clear = rel_gap(o["d1"], o["d2"]) > GAP
+    assert np.array_equal(idx[clear], o["c1"][clear])
+    same = idx == o["c1"]
+    assert np.abs(d1[same] - o["d1"][same]).max() <= 1e-5 * o["d1"].max()
+
+
+# Several chunks of samples, the last one short, with rows without halves in the
+# first and in a later one: by a memory cap that holds 512 rows (unit groups), and
+# by the chunk size itself (split columns: two chunks of 3,072 rows).
+@pytest.mark.parametrize("rows,cols,d,n,rows_in_cap", [(32, 40, 96, 3001, 512),
+                                                       (31, 41, 203, 1543, 300),
+                                                       (5, 25, 12000, 6000, 0)])
+@pytest.mark.parametrize("special", [False, True])
+def test_chunks_of_samples(rows, cols, d, n, rows_in_cap, special, monkeypatch):
+    torch = torch_cuda()
+    N = rows * cols
+    g = torch.Generator(device="cuda").manual_seed(d)
+    X = torch.randn(n, d, generator=g, device="cuda")
+    W = torch.randn(N, d, generator=g, device="cuda")
+    if special:
+        X[5, 3] = float("nan")
+        X[n - 2, 1] = 2.0 ** 45
+        X[n - 700] = 0.0
+    m = som.Map(rows, cols, d, seed=0)
+    m.weights = W
+    monkeypatch.setenv("SOM_BMU_ROUTE", "1")
+    a = [t.cpu().numpy() for t in m.bmu(X, second=True)]
+    monkeypatch.setenv("SOM_BMU_ROUTE", "2")
+    if rows_in_cap:
+        row, tiles = -(-d // 32) * 128, -(-N // 128)
+        cap = tiles * 128 * row + 4 * N + 2048 + rows_in_cap * (row + 4 + 32 * tiles)
+        monkeypatch.setenv("SOM_MAX_BYTES", str(cap))
+    assert m.bmu_route(n) == "halves"
+    b = [t.cpu().numpy() for t in m.bmu(X, second=True)]
+    monkeypatch.delenv("SOM_MAX_BYTES", raising=False)
+    say("chunks", rows, cols, d, n, "differing", int((a[0] != b[0]).sum()))
+    # the same units, or distances equal within fp32 rounding of a direct sum
+    for p, q in ((a[0], b[0]), (a[1], b[1])):
+        assert (p != q).mean() <= 1e-3
+    assert np.array_equal(np.isfinite(a[2]), np.isfinite(b[2]))
+    f = np.isfinite(a[2])
+    assert np.allclose(a[2][f], b[2][f], rtol=1e-5)
     m.close()
 
 
