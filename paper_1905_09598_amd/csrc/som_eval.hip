@@ -20,7 +20,7 @@
 // products in range order) and re-ranks them by direct fp32 distances
 // sum (x_j - w_j)^2, which fixes the BMU, the second BMU and the BMU's
 // squared distance.
-#include "som_internal.h"
+#include "som_candidates.h"
 
 #include <math.h>
 
@@ -40,25 +40,6 @@ constexpr int kBK = 64;
 constexpr int kPad = 4;
 constexpr int kLdsStride = kBK + kPad;  // floats per staged row
 constexpr int kEvalBlock = 256;
-
-__device__ inline bool better(float sa, int ua, float sb, int ub) {
-    return sa < sb || (sa == sb && (unsigned)ua < (unsigned)ub);
-}
-
-// Insert (s, u) into an ascending top-kCand list (u = -1 marks empty slots,
-// whose score is +inf).
-__device__ inline void insert_top(float (&ts)[kCand], int (&tu)[kCand], float s, int u) {
-    if (!better(s, u, ts[kCand - 1], tu[kCand - 1])) return;
-    ts[kCand - 1] = s;
-    tu[kCand - 1] = u;
-#pragma unroll
-    for (int i = kCand - 1; i > 0; --i) {
-        if (better(ts[i], tu[i], ts[i - 1], tu[i - 1])) {
-            float t = ts[i]; ts[i] = ts[i - 1]; ts[i - 1] = t;
-            int v = tu[i]; tu[i] = tu[i - 1]; tu[i - 1] = v;
-        }
-    }
-}
 
 struct EvalSmem {
     float xs[kBM * kLdsStride];

@@ -15,7 +15,7 @@
 // in fp64): Gaussian mixtures of d = 64, 500, 2048, 10000 7.1e-8, 1.55e-7,
 // 3.0e-7, 6.6e-7 and 5.7e-8, 1.0e-7, 1.9e-7, 4.3e-7; TF-IDF rows 4.2e-8, 3.8e-8,
 // 3.6e-8, 5.2e-8 and 3.5e-8, 2.8e-8, 3.0e-8, 2.7e-8.
-#include "som_internal.h"
+#include "som_candidates.h"
 
 #include <math.h>
 
@@ -115,22 +115,6 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float *X, int64_t
 
 typedef const __attribute__((address_space(1))) void *GlobalPtr;
 typedef __attribute__((address_space(3))) void *LdsPtr;
-
-__device__ inline bool better(float sa, int ua, float sb, int ub) {
-    return sa < sb || (sa == sb && (unsigned)ua < (unsigned)ub);
-}
-__device__ inline void insert_top(float (&ts)[kCand], int (&tu)[kCand], float s, int u) {
-    if (!better(s, u, ts[kCand - 1], tu[kCand - 1])) return;
-    ts[kCand - 1] = s;
-    tu[kCand - 1] = u;
-#pragma unroll
-    for (int i = kCand - 1; i > 0; --i) {
-        if (better(ts[i], tu[i], ts[i - 1], tu[i - 1])) {
-            float t = ts[i]; ts[i] = ts[i - 1]; ts[i - 1] = t;
-            int v = tu[i]; tu[i] = tu[i - 1]; tu[i - 1] = v;
-        }
-    }
-}
 
 // acc[a][b] = products over slabs [s0, s1) of units 16 a + 4 g .. (of the
 // wave's 64) with sample 16 b + i (of its 64), in the rows' scaled units.
