@@ -129,6 +129,7 @@ struct PanelArgs {
     float *gam[2];    // (m / 16) x npad x 16: coefficients of the panel's steps
     float *beta[2];   // (m / 16) x npad
     double *pc, *qc;  // npad x m, npad: products and Q at the panel's start
+    double *pz;       // npad: product with the next centre at the panel's start
     double *qn, *qe;   // npad: Q carried to the next panel; its estimate at the start
     unsigned *arrived;  // grid barrier of the exchanging kernel
     int32_t dpad, npad, ksplit, gsplit, prep, controllers, ctl_rows;

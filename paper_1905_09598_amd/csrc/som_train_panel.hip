@@ -548,11 +548,18 @@ __device__ inline void select_task(const PanelArgs &p, int64_t panel, int part, 
 
 // ----------------------------------------------------------------- correct
 
+// A panel's centre, as its step within the panel.
+__device__ inline int centre_of(const PanelArgs &p, int64_t panel) {
+    return __builtin_amdgcn_readfirstlane(__hip_atomic_load(
+        p.centre + (panel & 3), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
 // One wave: the products of units u0 .. u0 + 15 at panel `panel`'s start from
 // the sweep's partial products and panel - 1's coefficients, into pc and qc.
 // The coefficients' product runs from zero on the matrix instructions and is
 // added in fp64, so units far from the BMUs, whose gamma vanish, keep the
-// sweep's value exactly.
+// sweep's value exactly.  The next centre's column goes into pz; in its place
+// stands the own centre's, zero.
 template <int M>
 __device__ inline void correct_tile(const PanelArgs &p, int64_t panel, int u0) {
     constexpr int NT = M / 16;
@@ -560,6 +567,7 @@ __device__ inline void correct_tile(const PanelArgs &p, int64_t panel, int u0) {
     const int u = min(u0 + i, p.t.N - 1);
     const float *prod = p.prod[panel & 1], *gx = p.gx[panel % 3];
     const double *qf = p.qf[panel & 1];
+    const int z = centre_of(p, panel);
     f4 gam[NT], part[kMaxKSplit][NT];
     double q = 0.0;
     const double qn = p.qn[u], qe = p.qe[u];
@@ -595,6 +603,7 @@ __device__ inline void correct_tile(const PanelArgs &p, int64_t panel, int u0) {
         q = fma((double)bt * bt, q - qe, qn);
     }
     if (u0 + i < p.t.N) {
+        double next = 0.0;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             typedef double d2 __attribute__((ext_vector_type(2)));
@@ -606,11 +615,15 @@ __device__ inline void correct_tile(const PanelArgs &p, int64_t panel, int u0) {
                 for (int k = 1; k < kMaxKSplit; ++k)
                     v[e] += k < p.ksplit ? (double)part[k][t][e] : 0.0;
                 v[e] = fma((double)bt, v[e], (double)acc[t][e]);
+                const bool own = 16 * t + 4 * g + e == z;
+                next = own ? v[e] : next;
+                v[e] = own ? 0.0 : v[e];
             }
             d2 *to = reinterpret_cast<d2 *>(p.pc + (int64_t)u * M + 16 * t + 4 * g);
             to[0] = d2{v[0], v[1]};
             to[1] = d2{v[2], v[3]};
         }
+        if (g == (z >> 2 & 3)) p.pz[u] = next;
         if (g == 0) p.qc[u] = q;
     }
 }
@@ -730,10 +743,9 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
     float *cb = cg + (M / 16 - 1) * rows * kSub;               // [q][rows]
     const int64_t s0 = panel * M;
     // the centre's step; its column is the next centre's
-    const int z = __builtin_amdgcn_readfirstlane(__hip_atomic_load(
-        p.centre + (panel & 3), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    const int z = centre_of(p, panel);
     const int nst = steps_of<M>(p, panel);
-    const bool bad = a.state->order_bad != 0;  // used where the BMUs are traced
+    const bool bad = a.state->order_bad != 0;
 
     // The 16 steps' starting products of the lane's units, loaded a sub-block
     // ahead so that their round trip runs under the steps.
@@ -756,7 +768,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
         const int at = min(unit, a.N - 1);
         const double q = p.qc[at];
         Q[u] = unit < a.N ? q : (double)INFINITY;  // a unit past N is never nearest
-        Lz[u] = p.pc[(int64_t)at * M + z];
+        Lz[u] = p.pz[at];
         bsub[u] = 1.0;
         int r, c;
         unit_rc(at, a.cols, inv_cols, r, c);
@@ -806,6 +818,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
         __syncthreads();
     else
         __builtin_amdgcn_wave_barrier();
+    if (!GRID && bad) return true;  // unusable input, or an earlier panel was given up
     const double zz = (double)centre[M];  // |z' - z|^2
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -835,7 +848,7 @@ __device__ inline bool control_panel(const PanelArgs &p, int64_t panel, unsigned
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int k = 0; k < kSub; ++k)
-                L[u][k] = kSub * sub + k == z ? 0.0 : bsub[u] * ahead[u][k];
+                L[u][k] = bsub[u] * ahead[u][k];
         fetch(sub + 1 < M / 16 ? sub + 1 : sub);
         if (sub > 0) {
             // the panel's earlier coefficients, from zero in fp32
@@ -1121,7 +1134,6 @@ __global__ __launch_bounds__(64 * NW, 2) void panel_step_kernel(PanelArgs p, Sid
         side_task<M, TU, NW>(p, w, (int)blockIdx.x - 1, smem);
         return;
     }
-    if (p.t.state->order_bad) return;  // unusable input, or an earlier panel was given up
     if (!p.correct) {
         for (int t = threadIdx.x >> 6; t * 16 < p.t.N; t += NW) correct_tile<M>(p, panel, t * 16);
         __syncthreads();
@@ -1424,6 +1436,7 @@ int64_t panel_floats(const PanelPlan &pl, PanelArgs *p, float *base) {
     take(&a.qc, (int64_t)pl.npad);
     take(&a.qn, (int64_t)pl.npad);
     take(&a.qe, (int64_t)pl.npad);
+    take(&a.pz, (int64_t)pl.npad);
     take(&a.centre, (int64_t)64);
     take(&a.arrived, (int64_t)64);
     return off;
