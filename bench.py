@@ -29,7 +29,7 @@ of W's size on the training grid measured in the same run.  `bound` comes
 from the launch plan: the LDS-resident kernels never stream W and wait on
 the grid exchange ("latency"), the streamed ones stream W once per block
 ("hbm").  Training in panels, the default on every workload, touches W once
-per 48-80 steps and waits on its steps' chain ("latency"); `traffic` is then
+per 32-80 steps and waits on its steps' chain ("latency"); `traffic` is then
 null.
 `cpu_baseline` times the fp64 oracle on the host over a bounded prefix of
 the same training run.
@@ -52,26 +52,29 @@ TRAIN_SOURCES = [os.path.join(ROOT, "paper_1905_09598_amd", "csrc", f)
                  for f in ("som_device.h", "som_internal.h", "som_train.hip",
                            "som_train_pipe.h", "som_train_pipe.hip",
                            "som_train_pipe_stream.hip")]
+PANEL_SOURCES = [os.path.join(ROOT, "paper_1905_09598_amd", "csrc", f)
+                 for f in ("som_barrier.h", "som_device.h", "som_internal.h",
+                           "som_train_panel.hip")]
 
 
-def kernel_source_sha() -> str:
+def kernel_source_sha(panels: bool = False) -> str:
     """sha256 over the training kernels' sources (in a fixed order)."""
     h = hashlib.sha256()
-    for path in TRAIN_SOURCES:
+    for path in PANEL_SOURCES if panels else TRAIN_SOURCES:
         with open(path, "rb") as f:
             h.update(f.read())
     return h.hexdigest()
 
 
-def measured_traffic(workload: str):
+def measured_traffic(workload: str, panels: bool = False):
     """Counter-measured HBM bytes per launch, if taken on this kernel source."""
     try:
         with open(TRAFFIC_FILE) as f:
             rec = json.load(f)
     except (OSError, ValueError):
         return None
-    ent = rec.get(workload)
-    if not ent or ent.get("kernel_sha256") != kernel_source_sha():
+    ent = rec.get(workload + ("/panels" if panels else ""))
+    if not ent or ent.get("kernel_sha256") != kernel_source_sha(panels):
         return None
     return ent.get("bytes_per_launch")
 
@@ -184,6 +187,7 @@ def map_sweep(cpu_budget: float):
         N = side * side
         m = som.Map(side, side, d, seed=0)
         plan = m.plan()
+        panels = m.train_route(n) == "panels"
         kw = dict(order=od)
         m.train(Xd, 1, 0.5, 0.01, side / 2.0, 1.0, **kw)  # warm-up
         times = []
@@ -197,8 +201,9 @@ def map_sweep(cpu_budget: float):
         t = sorted(times)[1]
         line = {"map": f"{side}x{side}", "units": N, "d": d, "steps": n,
                 "us_per_step": t / n * 1e6, "proto_dim_updates_per_s": n * N * d / t,
-                "train_s": t, "grid": plan["grid"],
-                "variant": ["stream", "lds", "pipelined-stream", "pipelined-lds",
+                "train_s": t, "grid": None if panels else plan["grid"],
+                "variant": "panels" if panels else
+                           ["stream", "lds", "pipelined-stream", "pipelined-lds",
                             "pipelined-stream-cols"][plan["variant"]]}
         if cpu_budget > 0:
             W = oracle.init_uniform(0, N, d)
@@ -467,7 +472,7 @@ def measure(cfg, input_kind: str, steps: int, warmup: int):
     panels = not sparse and m.train_route(cfg.steps) == "panels"
     if panels:
         kernel_name = "panel_step_kernel" if cfg.units <= 1024 else "panel_grid_kernel"
-        variant, bound, traffic = "panels", "latency", None
+        variant, bound, traffic = "panels", "latency", measured_traffic(cfg.name, panels=True)
     if sparse:
         # the sparse path's own bytes: the dense 3 N d 4 per step does not
         # describe a kernel that touches only the sample's features
@@ -503,8 +508,8 @@ def measure(cfg, input_kind: str, steps: int, warmup: int):
         roof["frac_applicable"] = phys / ref["GB/s"]
     if sparse:
         roof["note"] = ("sparse path: bytes = the samples' non-zeros gathered and scattered in "
-                        "fp64 for every unit; its step is bound by the grid exchange's latency, "
-                        "not by bytes")
+                        "fp64 for every unit; its step is bound by the compute wave's issue, "
+                        "beside the grid exchange, not by bytes")
     res = {
         "value": updates / (ms_per_step / 1e3),
         "ms_per_step": ms_per_step,

@@ -146,21 +146,23 @@ som_status som_set_stream(som_map *map, void *stream);
 
 /* Online training (paper Sec. 5A and 6C): epochs * n steps over the n x d
  * row-major fp32 device matrix X, the whole per-sample loop on the device.
- * Stream-ordered.  Calls train in panels of 48 to 80 steps where that is the
- * faster way (maps of up to 16,384 units, beyond 2,560 units rows of up to 3,072
- * floats; not short calls, and not maps of more than 700 units whose rows fit in
- * LDS few to a workgroup): the steps run
- * on inner products while the prototypes are read and written once a panel
- * (one launch or two per panel up to 1,024 units, one cooperative kernel for
- * the call beyond), with up to about 16 N M + 8 M d floats of work memory (M
- * steps a panel) that the map keeps for later calls.  All others, calls whose
- * work memory would exceed SOM_MAX_BYTES and calls with a launch shape forced
- * from the environment take one persistent cooperative kernel (the shape
+ * Stream-ordered.  Calls train in panels of 32 to 80 steps where that is the
+ * faster way (maps of up to 16,384 units, beyond 2,560 units rows of up to
+ * 3,072 floats; not short calls, and not maps of more than 700 units whose
+ * rows fit in LDS few to a workgroup): the steps run on inner products while
+ * the prototypes are read and written once a panel (one launch or two per
+ * panel up to 1,024 units, so that a call of more than about 50,000 steps
+ * waits until the runtime has taken its last launches; one cooperative
+ * kernel for the call beyond), with up to about 16 N M + 8 M d floats of
+ * work memory (M steps a panel) that the map keeps for later calls.  All
+ * others, calls whose work memory would exceed SOM_MAX_BYTES or finds no
+ * room on the device, and calls with a launch shape forced from the
+ * environment take one persistent cooperative kernel (the shape
  * som_train_plan reports); for it, when d is not a multiple of 4 or X is not
- * 16-byte aligned, X is first copied into a buffer of n * roundup(d, 4) floats
- * that the map keeps for later calls, and when its plan is the long-row kernel
- * (variant 4) and the prototypes' row pitch exceeds d, into a buffer of n rows
- * of that pitch (zero past d).
+ * 16-byte aligned, X is first copied into a buffer of n * roundup(d, 4)
+ * floats that the map keeps for later calls, and when its plan is the long-
+ * row kernel (variant 4) and the prototypes' row pitch exceeds d, into a
+ * buffer of n rows of that pitch (zero past d).
  * Errors: SOM_E_ARG (map, X or sched NULL, n <= 0, epochs <= 0, epochs * n
  * beyond 2^31 - 1, bad decay kind, lr < 0 or not finite, sigma < 0 or NaN,
  * exponential decay with a zero or infinite endpoint, total_steps too small,
@@ -257,8 +259,9 @@ som_status som_bmu2(som_map *map, const float *X, int64_t n, int32_t *out_idx,
 
 /* As som_bmu2, for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the same search with its products in fp32 and the same outputs, but no hipMalloc, hipFree or
- * allocating library routine is called.  The call's scratch (the
+ * the same search with its products always in fp32 (so a BMU can differ where
+ * two units are equally near within fp32 rounding), but no hipMalloc, hipFree
+ * or allocating library routine is called.  The call's scratch (the
  * prototypes' squared norms, the BMUs when out_idx is NULL, the candidate
  * lists, and the partial products when the search splits d) lives in one
  * fixed 8 MiB array per device, held from the library's load until the

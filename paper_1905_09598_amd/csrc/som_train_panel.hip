@@ -43,8 +43,8 @@
 // here the pass runs once per M steps beside the steps, and maps of up to 1024
 // units need no exchange.  Measured, microseconds per step with those kernels
 // and here: 10 x 10 units of 500 floats 1.26 and 0.66, 11 x 11 of 4545 1.54 and
-// 0.89, 30 x 30 of 5000 2.18 and 1.57, 50 x 50 of 10000 6.35 and 3.21, 100 x 100
-// of 2048 4.33 and 2.98.
+// 0.91, 30 x 30 of 5000 2.18 and 1.60, 50 x 50 of 10000 6.35 and 3.25, 100 x 100
+// of 2048 4.33 and 3.00.
 #include "som_barrier.h"
 #include "som_device.h"
 

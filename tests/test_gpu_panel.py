@@ -53,13 +53,13 @@ def _train(rows, cols, d, n, topology=som.RECT, sched=(0.4, 0.02, None, 0.5), of
                          total_steps=total or step0 + n)
     Ds = np.sort(oracle.distances(Wk, X[order[k]]))
     say(f"  identical BMUs for {k}/{n} steps")
-    # (thousands of units on rows of one to three floats lie so close together that
+    # (thousands of units on rows of one float lie so close together that
     # their distances, differences of fp32 sums at the scale S of squared
     # sample-to-sample distances within about 8 roundings of 2^-24 S, are not told
     # apart below 1e-6 S; neither are they by the pipelined kernels' sums)
     S = np.square(X.astype(np.float64) - X[order[0]]).sum(1).max()
     assert len(Ds) > 1 and (Ds[1] - Ds[0] <= GAP * Ds[0] or
-                            (d < 4 and Ds[1] - Ds[0] <= 1e-6 * S)), "divergence without a near tie"
+                            (d == 1 and Ds[1] - Ds[0] <= 1e-6 * S)), "divergence without a near tie"
 
 
 @pytest.mark.parametrize("rows,cols", [(1, 1), (1, 15), (4, 4), (1, 17), (8, 8), (5, 13),
