@@ -57,6 +57,7 @@ using namespace dev;
 constexpr int kSub = 16;         // steps whose L columns a lane holds at a time
 constexpr int kSweepDims = 32;   // columns a sweep wave takes at a time (two tiles)
 constexpr int kMaxKSplit = 4;    // column ranges of the pass over the prototypes
+constexpr int kChain = 2;        // groups of 32 columns between two sums of a sweep wave
 constexpr int kGatherDims = 64;  // columns of one gather task
 constexpr int kPrepThreads = 256;
 constexpr int kTPitch = kSub + 4;
@@ -118,8 +119,13 @@ struct SweepTile {
 // One task: units 16 TU ugrp .., column range kpart of p.ksplit; panel
 // `panel` - 1's updates applied (APPLY) and the products with panel `panel` +
 // 1's columns written (PROD).  Wave w of BW takes 32 columns at a time (a whole
-// 128-byte line of each row); the waves' partial products are added through
-// LDS.
+// 128-byte line of each row).  Its products go to sums in LDS every 64 columns,
+// and the waves' sums are added in fp64: in one chain of fp32 additions over all
+// of a wave's columns the rounding of the last ones, at full magnitude, added up.
+// Steps off the fp64 minimum on tight clusters (8 of spread 0.02 at unit
+// distances), of 400, one chain, sums and the pipelined kernel: 100 x 100 units of
+// 2048 floats 55, 25 and 27, 50 x 50 of 10000 87, 40 and 33; the sums cost nothing
+// that shows.
 //
 // What bounds it: the 2 * 2 M N d flops of a panel on the fp32 matrix
 // instructions (16x16x4: 32 cycles for 1024 multiply-adds), M / 2 of them per
@@ -138,6 +144,11 @@ __device__ inline void sweep_task(const PanelArgs &p, int64_t panel, int ugrp, i
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int i = lane & 15, g = lane >> 4;
     const int u0 = ugrp * 16 * TU;
+    // the waves' sums of products, [BW][TU NT][64], and of squares, [BW][16 TU]
+    f4 *sums = reinterpret_cast<f4 *>(smem);
+    double *qred = reinterpret_cast<double *>(sums + BW * TU * NT * 64);
+    f4 *own = sums + wave * TU * NT * 64 + lane;
+    if constexpr (PROD) __syncthreads();  // (a workgroup's earlier task may still read them)
     f4 gam[TU][NT];
     float bt[TU];
     if constexpr (APPLY)
@@ -227,6 +238,17 @@ __device__ inline void sweep_task(const PanelArgs &p, int64_t panel, int ugrp, i
                                                                           acc[tu][t], 0, 0, 0);
         }
     };
+    // The products so far to the wave's sums, which start at zero.
+    const auto flush = [&](bool first) {
+#pragma unroll
+        for (int tu = 0; tu < TU; ++tu)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                f4 *to = own + (tu * NT + t) * 64;
+                *to = first ? acc[tu][t] : *to + acc[tu][t];
+                acc[tu][t] = f4{0.f, 0.f, 0.f, 0.f};
+            }
+    };
     if (mine > 0) {
         Tile t0, t1;
         load(t0, 0);
@@ -235,47 +257,38 @@ __device__ inline void sweep_task(const PanelArgs &p, int64_t panel, int ugrp, i
             compute(t0, n);
             load(t0, n + 2);  // past the end: the last group again, unused
             compute(t1, n + 1);
+            if constexpr (PROD)
+                if ((n >> 1) % kChain == kChain - 1) flush(n >> 1 == kChain - 1);
         }
     }
     if constexpr (PROD) {
-        // add the waves' partial products pairwise, in a fixed order
-        f4 *red = reinterpret_cast<f4 *>(smem);
-        double *qred = reinterpret_cast<double *>(red + BW / 2 * TU * NT * 64);  // [BW][16 TU]
-        __syncthreads();  // (a workgroup's earlier task may still read them)
+        flush(mine < kChain);
 #pragma unroll
         for (int tu = 0; tu < TU; ++tu) {
             q[tu] += __shfl_xor(q[tu], 16, 64);
             q[tu] += __shfl_xor(q[tu], 32, 64);
             if (g == 0) qred[wave * 16 * TU + 16 * tu + i] = q[tu];
         }
-#pragma unroll
-        for (int half = BW / 2; half >= 1; half /= 2) {
-            if (wave >= half && wave < 2 * half)
-#pragma unroll
-                for (int tu = 0; tu < TU; ++tu)
-#pragma unroll
-                    for (int t = 0; t < NT; ++t)
-                        red[(((wave - half) * TU + tu) * NT + t) * 64 + lane] = acc[tu][t];
-            __syncthreads();
-            if (wave < half)
-#pragma unroll
-                for (int tu = 0; tu < TU; ++tu)
-#pragma unroll
-                    for (int t = 0; t < NT; ++t)
-                        acc[tu][t] = acc[tu][t] + red[((wave * TU + tu) * NT + t) * 64 + lane];
-            if (half > 1) __syncthreads();
-        }
+        __syncthreads();
+        // the waves' sums added in order, a share of them by each wave
         float *prod = p.prod[(panel + 1) & 1];
         double *qf = p.qf[(panel + 1) & 1];
-        if (wave == 0) {
+        for (int e = wave; e < TU * NT; e += BW) {
+            double v[4];
 #pragma unroll
-            for (int tu = 0; tu < TU; ++tu) {
-                const int64_t row = (int64_t)kpart * p.npad + u0 + 16 * tu + i;
+            for (int k = 0; k < 4; ++k) v[k] = sums[e * 64 + lane][k];
 #pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    *reinterpret_cast<f4 *>(prod + row * M + 16 * t + 4 * g) = acc[tu][t];
+            for (int w = 1; w < BW; ++w) {
+                const f4 x = sums[(w * TU * NT + e) * 64 + lane];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[k] += (double)x[k];
             }
-        } else if (wave == 1 && lane < 16 * TU) {
+            const int tu = e / NT, t = e - tu * NT;
+            const int64_t row = (int64_t)kpart * p.npad + u0 + 16 * tu + i;
+            *reinterpret_cast<f4 *>(prod + row * M + 16 * t + 4 * g) =
+                f4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+        }
+        if (wave == BW - 1 && lane < 16 * TU) {
             double s = qred[lane];
 #pragma unroll
             for (int w = 1; w < BW; ++w) s += qred[w * 16 * TU + lane];
@@ -286,7 +299,7 @@ __device__ inline void sweep_task(const PanelArgs &p, int64_t panel, int ugrp, i
 
 template <int M, int TU, int BW>
 constexpr size_t sweep_lds() {
-    return (size_t)BW / 2 * TU * (M / 16) * 64 * 16 + (size_t)BW * 16 * TU * 8;
+    return (size_t)BW * TU * (M / 16) * 64 * 16 + (size_t)BW * 16 * TU * 8;
 }
 
 // Sweep task t of a panel: unit group t / ksplit, column range t % ksplit.

@@ -167,6 +167,39 @@ def test_outliers_do_not_cost_the_other_steps_their_bmus(rows, cols, M, factor):
     assert np.abs(W - Wk).max() <= 1e-6 * np.abs(X).max()
 
 
+# Tight clusters far apart, where many units are nearly as near as the BMU: the
+# rounding of a distance stays within 6 roundings 2^-24 of the largest
+# sample-to-sample distance S (the pipelined kernel: 2 to 6; one chain of fp32 sums
+# over a wave's columns: 12).
+@pytest.mark.parametrize("rows,cols,d", [(100, 100, 2048), (30, 30, 5000)])
+def test_rounding_of_distances_on_tight_clusters(rows, cols, d):
+    import torch
+    n, N = 300, rows * cols
+    g = torch.Generator(device="cuda").manual_seed(d)
+    C = torch.randn(8, d, generator=g, device="cuda")
+    pick = lambda k: C[torch.randint(0, 8, (k,), generator=g, device="cuda")]
+    X = pick(n) + 0.02 * torch.randn(n, d, generator=g, device="cuda")
+    W0 = pick(N) + 0.005 * torch.randn(N, d, generator=g, device="cuda")
+    order = torch.arange(n, device="cuda", dtype=torch.int32)
+    trace = torch.full((n,), -1, device="cuda", dtype=torch.int32)
+    m = som.Map(rows, cols, d, seed=0)
+    m.weights = W0
+    m.train(X, 1, 0.1, 0.02, 3.0, 1.0, order=order, bmu_trace=trace)
+    m.synchronize()
+    m.close()
+    S = float(torch.cdist(X.double(), X.double()).max()) ** 2
+    W, sched = W0.double(), oracle.schedule(0.1, 0.02, 3.0, 1.0)
+    worst = 0.0
+    for k, c in enumerate(trace.tolist()):
+        diff = X[k].double() - W
+        D = diff.square().sum(1)
+        worst = max(worst, float(D[c] - D.min()))
+        h = oracle.neighbourhood(rows, cols, som.RECT, c, *oracle.schedule_at(k, n, sched))
+        W += torch.from_numpy(h).cuda()[:, None] * diff
+    say("tight clusters", rows, cols, d, "largest excess", worst / S * 2 ** 24, "x 2^-24 S")
+    assert worst <= 6 * 2.0 ** -24 * S
+
+
 @pytest.mark.parametrize("rows,cols", [(9, 11), (60, 50)])
 def test_resumed_steps_follow_the_oracle(rows, cols):
     _train(rows, cols, 32, 100, step0=37, total=500)
