@@ -294,9 +294,7 @@ som_status run_eval_half(som_map *m, som::EvalArgs a, const som::HalfPlan &h, in
     a.bad = bad;
     a.x_vec4 = (m->d % 4 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0);
     e = som::launch_row_sqnorm(m->W, m->ld, m->N, m->wnorm, bad, m->stream);
-    if (e == hipSuccess)
-        e = som::launch_split_rows(m->W, a.N, m->ld, a.d, som::kHalfUnits, m->half + at.w, wscale,
-                                   bad, true, m->stream);
+    const som::SplitRows protos{m->W, a.N, m->ld, som::kHalfUnits, true, m->half + at.w, wscale, bad};
     for (int64_t i0 = 0; i0 < n && e == hipSuccess; i0 += h.chunk) {
         a.n = n - i0 < h.chunk ? n - i0 : h.chunk;
         a.X = X + i0 * a.d;
@@ -304,8 +302,9 @@ som_status run_eval_half(som_map *m, som::EvalArgs a, const som::HalfPlan &h, in
         a.idx1 = idx1 + i0;
         a.idx2 = idx2 ? idx2 + i0 : nullptr;
         a.d1 = d1 ? d1 + i0 : nullptr;
-        e = som::launch_split_rows(a.X, a.n, a.d, a.d, som::kHalfSamples, m->half + at.x, xscale,
-                                   bad + 1, false, m->stream);
+        const som::SplitRows samples{a.X,   a.n,    a.d, som::kHalfSamples, false, m->half + at.x,
+                                     xscale, bad + 1};
+        e = som::launch_split_rows(i0 == 0 ? &protos : nullptr, samples, a.d, m->stream);
         if (e == hipSuccess) e = som::launch_bmu_half(a, m->stream);
         if (e == hipSuccess) e = som::launch_bmu_unsplit(a, m->num_cus, m->stream);
         if (e == hipSuccess) e = som::launch_bmu_rerank(a, m->stream);

@@ -47,15 +47,22 @@ constexpr float kRowLo = 0x1p-40f, kRowHi = 0x1p40f;       // row maxima that ar
 // small keeps the scale of 2^-40: its halves are then exact to 2^-79, far below a
 // rounding of the distance to a sample that is not as small.
 // scale[row] = 2^-k; rows past `rows` are zero.  Bound by memory: the rows are
-// read twice, the second time from L2, and written once.
+// read twice, the second time from L2, and written once.  The first `ablocks`
+// workgroups take a's rows, the others b's: the prototypes and the first samples
+// in one launch.
 template <bool VEC4>
-__global__ __launch_bounds__(256) void split_rows_kernel(const float *X, int64_t rows, int64_t ld,
-                                                         int32_t d, int32_t slabs, _Float16 *out,
-                                                         float *scale, int32_t *bad,
-                                                         bool small_ok) {
+__global__ __launch_bounds__(256) void split_rows_kernel(SplitRows a, SplitRows b, int ablocks,
+                                                         int32_t d, int32_t slabs) {
     __shared__ float mul[16];
     const int t = threadIdx.x, r = t >> 4, c0 = t & 15;
-    const int64_t row0 = (int64_t)blockIdx.x * 16;
+    const bool first = (int)blockIdx.x < ablocks;
+    const int64_t block = first ? blockIdx.x : blockIdx.x - ablocks;
+    const float *X = first ? a.X : b.X;
+    const int64_t rows = first ? a.rows : b.rows, ld = first ? a.ld : b.ld;
+    float *scale = first ? a.scale : b.scale;
+    int32_t *bad = first ? a.bad : b.bad;
+    const bool small_ok = first ? a.small_ok : b.small_ok;
+    const int64_t row0 = block * 16;
     const auto load4 = [&](const float *x, int c) {
         f4 v;
         if (VEC4) {
@@ -97,7 +104,8 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float *X, int64_t
     const int64_t row = row0 + i < rows ? row0 + i : rows - 1;
     const float m = row0 + i < rows ? mul[i] : 0.f;
     const float *x = X + row * ld;
-    h8 *to = reinterpret_cast<h8 *>(out + (int64_t)blockIdx.x * slabs * kBlockHalves);
+    _Float16 *out = static_cast<_Float16 *>(first ? a.out : b.out);
+    h8 *to = reinterpret_cast<h8 *>(out + block * slabs * kBlockHalves);
     for (int s = wave; s < slabs; s += 4) {
         const int c = s * kHK + 8 * g;
         const f4 a = load4(x, c), b = load4(x, c + 4);
@@ -379,15 +387,21 @@ bool plan_bmu_half(EvalArgs *a, int num_cus, uint64_t max_bytes, double fp32_us,
     return (double)chunks * (best + kLaunchUs) + rows_us + kLaunchUs < fp32_us;
 }
 
-hipError_t launch_split_rows(const float *X, int64_t rows, int64_t ld, int32_t d, int tile,
-                             void *out, float *scale, int32_t *bad, bool small_ok,
+hipError_t launch_split_rows(const SplitRows *first, const SplitRows &second, int32_t d,
                              hipStream_t s) {
-    const int32_t slabs = (int32_t)ceil_div(d, kHK);
-    const dim3 grid((unsigned)(ceil_div(rows, tile) * (tile / 16)));
-    const bool vec4 = d % 4 == 0 && ld % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
-    (vec4 ? split_rows_kernel<true> : split_rows_kernel<false>)
-        <<<grid, dim3(256), 0, s>>>(X, rows, ld, d, slabs, static_cast<_Float16 *>(out), scale,
-                                    bad, small_ok);
+    const auto blocks = [](const SplitRows &r) { return ceil_div(r.rows, r.tile) * (r.tile / 16); };
+    const auto vec4 = [d](const SplitRows &r) {
+        return d % 4 == 0 && r.ld % 4 == 0 && reinterpret_cast<uintptr_t>(r.X) % 16 == 0;
+    };
+    if (first && vec4(*first) != vec4(second)) {
+        const hipError_t e = launch_split_rows(nullptr, *first, d, s);
+        if (e != hipSuccess) return e;
+        first = nullptr;
+    }
+    const int ablocks = first ? (int)blocks(*first) : 0;
+    (vec4(second) ? split_rows_kernel<true> : split_rows_kernel<false>)
+        <<<dim3((unsigned)(ablocks + blocks(second))), dim3(256), 0, s>>>(
+            first ? *first : second, second, ablocks, d, (int32_t)ceil_div(d, kHK));
     return hipGetLastError();
 }
 

@@ -210,10 +210,19 @@ bool plan_bmu_half(EvalArgs *a, int num_cus, uint64_t max_bytes, double fp32_us,
 int64_t half_lists_bytes(const HalfPlan &plan, int64_t rows, int32_t N);
 // Halves that `rows` rows take, stored in whole tiles of `tile` rows.
 int64_t half_rows_halves(int64_t rows, int32_t d, int tile);
-// Split the rows of X (row pitch ld) into out, their scales into scale; *bad is
-// raised by a row that cannot be split (with small_ok, rows of tiny values can).
-hipError_t launch_split_rows(const float *X, int64_t rows, int64_t ld, int32_t d, int tile,
-                             void *out, float *scale, int32_t *bad, bool small_ok,
+// Rows to be split: `rows` of X (row pitch ld), into out in whole tiles of `tile`
+// rows, their scales into scale; *bad is raised by a row that has no halves.
+struct SplitRows {
+    const float *X;
+    int64_t rows, ld;
+    int32_t tile;
+    bool small_ok;  // rows of small magnitudes are split all the same
+    void *out;
+    float *scale;
+    int32_t *bad;
+};
+// `first` (nullable) and `second`, of d columns.
+hipError_t launch_split_rows(const SplitRows *first, const SplitRows &second, int32_t d,
                              hipStream_t s);
 hipError_t launch_bmu_half(const EvalArgs &a, hipStream_t s);
 // After launch_bmu_half: the fp32 products in its place where a.bad says so.
