@@ -151,18 +151,18 @@ som_status som_set_stream(som_map *map, void *stream);
  * 3,072 floats; not short calls, and not maps of more than 700 units whose
  * rows fit in LDS few to a workgroup): the steps run on inner products while
  * the prototypes are read and written once a panel (one launch or two per
- * panel up to 1,024 units, so that a call of more than about 50,000 steps
- * waits until the runtime has taken its last launches; one cooperative
- * kernel for the call beyond), with up to about 16 N M + 8 M d floats of
- * work memory (M steps a panel) that the map keeps for later calls.  All
- * others, calls whose work memory would exceed SOM_MAX_BYTES or finds no
- * room on the device, and calls with a launch shape forced from the
- * environment take one persistent cooperative kernel (the shape
- * som_train_plan reports); for it, when d is not a multiple of 4 or X is not
- * 16-byte aligned, X is first copied into a buffer of n * roundup(d, 4)
- * floats that the map keeps for later calls, and when its plan is the long-
- * row kernel (variant 4) and the prototypes' row pitch exceeds d, into a
- * buffer of n rows of that pitch (zero past d).
+ * panel up to 1,024 units, so that a call of more than some 20,000 steps,
+ * 110,000 up to 256 units, waits until the runtime has taken its last
+ * launches; one cooperative kernel for the call beyond), with up to about 16
+ * N M + 8 M d floats of work memory (M steps a panel) that the map keeps for
+ * later calls.  All others, calls whose work memory would exceed
+ * SOM_MAX_BYTES or finds no room on the device, and calls with a launch
+ * shape forced from the environment take one persistent cooperative kernel
+ * (the shape som_train_plan reports); for it, when d is not a multiple of 4
+ * or X is not 16-byte aligned, X is first copied into a buffer of n *
+ * roundup(d, 4) floats that the map keeps for later calls, and when its plan
+ * is the long-row kernel (variant 4) and the prototypes' row pitch exceeds
+ * d, into a buffer of n rows of that pitch (zero past d).
  * Errors: SOM_E_ARG (map, X or sched NULL, n <= 0, epochs <= 0, epochs * n
  * beyond 2^31 - 1, bad decay kind, lr < 0 or not finite, sigma < 0 or NaN,
  * exponential decay with a zero or infinite endpoint, total_steps too small,
